@@ -319,35 +319,93 @@ __device__ void block_exclusive_scan(const uint32_t* in, int R, uint32_t* wsum, 
   }
 }
 
-// start[key] = exclusive scan of count, cursor = start, bucket cursor
-// bcur[b] = start[b * S^3] (one workgroup)
+// Exclusive scan of the tile counts by one workgroup of 1024 threads: start =
+// cursor = scan, and with bcur the bucket cursors bcur[b] = start[b << bshift].  Slabs of 4096 U tiles,
+// 4 U consecutive ones per thread as 16-byte loads that are all in flight at
+// once (one load at a time took 75 us for the 32768 tiles of a 512^3 mesh, two
+// slabs of U = 4 take 13); ntiles is a power of 8, the arrays are 256-byte
+// aligned.
+template <int U>
+__device__ __forceinline__ void tile_scan(const uint32_t* __restrict__ count, int ntiles, int bshift,
+                                          uint32_t* __restrict__ start, uint32_t* __restrict__ cursor,
+                                          uint32_t* __restrict__ bcur, uint32_t* wsum) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  uint32_t base = 0;
+  for (int t0 = 0; t0 < ntiles; t0 += 4096 * U) {
+    const int t = t0 + (int)threadIdx.x * 4 * U;
+    uint32_t c[4 * U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      uint4 q = make_uint4(0u, 0u, 0u, 0u);
+      if (t + 4 * u < ntiles) q = *reinterpret_cast<const uint4*>(count + t + 4 * u);
+      c[4 * u] = q.x; c[4 * u + 1] = q.y; c[4 * u + 2] = q.z; c[4 * u + 3] = q.w;
+    }
+    uint32_t s = 0;
+#pragma unroll
+    for (int e = 0; e < 4 * U; ++e) s += c[e];
+    uint32_t v = s;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t u = __shfl_up(v, off, 64);
+      if (lane >= off) v += u;
+    }
+    if (t0) __syncthreads();  // wsum of the previous slab is read
+    if (lane == 63) wsum[wv] = v;
+    __syncthreads();
+    uint32_t w = wsum[lane & 15];  // inclusive scan of the 16 wave totals in every wavefront
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+      const uint32_t u = __shfl_up(w, off, 16);
+      if ((lane & 15) >= off) w += u;
+    }
+    uint32_t run = base + v - s + (wv ? __shfl(w, wv - 1, 64) : 0u);
+    base += __shfl(w, 15, 64);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      uint4 q;
+      q.x = run; run += c[4 * u];
+      q.y = run; run += c[4 * u + 1];
+      q.z = run; run += c[4 * u + 2];
+      q.w = run; run += c[4 * u + 3];
+      const int tt = t + 4 * u;
+      if (tt + 3 < ntiles) {
+        *reinterpret_cast<uint4*>(start + tt) = q;
+        *reinterpret_cast<uint4*>(cursor + tt) = q;
+      } else if (tt < ntiles) {  // a mesh of one tile
+        start[tt] = q.x;
+        cursor[tt] = q.x;
+      }
+      if (bcur) {
+        const uint32_t r[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (tt + e < ntiles && ((tt + e) & ((1 << bshift) - 1)) == 0) bcur[(tt + e) >> bshift] = r[e];
+      }
+    }
+  }
+}
+
+template <int U>
 __global__ void __launch_bounds__(1024) k_tile_scan(const uint32_t* __restrict__ count, int ntiles,
-                                                    int per_bucket, uint32_t* __restrict__ start,
+                                                    int bshift, uint32_t* __restrict__ start,
                                                     uint32_t* __restrict__ cursor,
                                                     uint32_t* __restrict__ bcur) {
   __shared__ uint32_t wsum[16];
-  block_exclusive_scan<1024>(count, ntiles, wsum, [&](int t, uint32_t v) {
-    start[t] = v;
-    cursor[t] = v;
-    if (t % per_bucket == 0) bcur[t / per_bucket] = v;
-  });
+  tile_scan<U>(count, ntiles, bshift, start, cursor, bcur, wsum);
 }
 
 // k_tile_scan (workgroup 0) and, in workgroups 1 .. CNPC_SUMS_LEN, the
 // fixed-order column sums of k_reduce_partials (first wavefront): the two
 // steps between the first and the second sort step of a fused sort, one launch.
+template <int U>
 __global__ void __launch_bounds__(1024) k_tile_scan_sums(const uint32_t* __restrict__ count, int ntiles,
-                                                         int per_bucket, uint32_t* __restrict__ start,
-                                                         uint32_t* __restrict__ cursor, uint32_t* __restrict__ bcur,
+                                                         uint32_t* __restrict__ start,
+                                                         uint32_t* __restrict__ cursor,
                                                          const double* __restrict__ partial, int nblocks,
                                                          double* __restrict__ sums) {
   __shared__ uint32_t wsum[16];
   if (blockIdx.x == 0) {
-    block_exclusive_scan<1024>(count, ntiles, wsum, [&](int t, uint32_t v) {
-      start[t] = v;
-      cursor[t] = v;
-      if (t % per_bucket == 0) bcur[t / per_bucket] = v;
-    });
+    tile_scan<U>(count, ntiles, 0, start, cursor, nullptr, wsum);
     return;
   }
   if (threadIdx.x >= 64) return;
@@ -467,7 +525,8 @@ __global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ p
 // bcnt[b] and sends whatever would pass the capacity to the overflow region
 // (reserved on *ovf), which the tile pass takes as chunks of mixed buckets.
 // Persistent workgroups walk chunks of NT * PER particles, so the LDS tile
-// histogram is flushed with one atomic per non-empty tile per workgroup.  With
+// histogram is flushed with one atomic per non-empty tile per workgroup; with
+// more tiles than LDS_TILES_MAX k_region_count counts them afterwards.  With
 // `pack` (FP32 painter, unweighted, 256^3 and more, at most 2^16 tiles) a
 // record goes out as pack_rec in 8 bytes and its tile index in 2 more, in an
 // array after the 8-byte records of its region (both fit the 12-byte records'
@@ -479,7 +538,7 @@ struct BucketArgs {
   uint32_t cap;       // records per bucket region
   uint32_t* bcnt;     // [nbuckets] reservations per bucket (may exceed cap)
   uint32_t* ovf;      // overflow records reserved
-  uint32_t* tcount;   // [ntiles] tile histogram
+  uint32_t* tcount;   // [ntiles] tile histogram (filled here up to LDS_TILES_MAX tiles)
   double* partial;    // [gridDim.x][CNPC_SUMS_LEN] catalog-sum partials
   bool pack;          // records out as pack_rec + a 16-bit tile index (rkey / okey)
   uint16_t* rkey;     // [nbuckets * cap] tile index of each region record (pack)
@@ -558,7 +617,6 @@ __global__ void __launch_bounds__(NT) k_bucket_pass(const uint32_t* __restrict__
         tk[k] = t;
         key[k] = t >> bshift;
         if (lds_tiles) atomicAdd(&ltile[t], 1u);
-        else atomicAdd(&ba.tcount[t], 1u);
         rank[k] = atomicAdd(&hist[key[k]], 1u);
         const double wi = RS == 4 ? (double)__uint_as_float(r[k].v[3]) : 1.0;
         sums_add<LMAX>(acc, r[k].v[0], r[k].v[1], r[k].v[2], wi, scale, sa);
@@ -633,6 +691,70 @@ __global__ void __launch_bounds__(NT) k_bucket_pass(const uint32_t* __restrict__
       const uint32_t c = ltile[t];
       if (c) atomicAdd(&ba.tcount[t], c);
     }
+}
+
+// Tile histogram of bucket-sorted records, for meshes of more tiles than the
+// bucket pass holds in LDS (512^3 and more).  A bucket's records fall into its
+// own S^3 <= 64 tiles, so a workgroup counts REGION_CHUNK of them in LDS (one
+// copy per wavefront) and adds each tile once; only the overflow records take
+// an atomic each.  Bound by its reads: the 16-bit tile indices of packed
+// records (2 bytes a particle) or the records themselves (12 or 16).  One
+// global atomic per particle in the bucket pass, which it replaces, held that
+// pass to 2.6 ms for 5.5e7 particles (0.90 ms without it, and 0.04 ms here; 3.3e8
+// full records: 0.80 ms here).
+constexpr int REGION_CHUNK = 65536;
+template <int RS>
+__global__ void __launch_bounds__(1024) k_region_count(const Rec<RS>* __restrict__ region,
+                                                       const uint16_t* __restrict__ rkey,
+                                                       const Rec<RS>* __restrict__ ovf_in,
+                                                       const uint16_t* __restrict__ okey,
+                                                       const uint32_t* __restrict__ bcnt,
+                                                       const uint32_t* __restrict__ ovf, uint32_t cap,
+                                                       int chunks_per_bucket, int nbuckets, TileGeom g, bool packed,
+                                                       uint32_t* __restrict__ count) {
+  __shared__ uint32_t hist[16][64];
+  const int nreg = nbuckets * chunks_per_bucket;
+  if ((int)blockIdx.x >= nreg) {
+    const uint32_t no = *ovf;
+    for (uint32_t i = (blockIdx.x - nreg) * 1024u + threadIdx.x; i < no; i += (gridDim.x - nreg) * 1024u) {
+      int t;
+      if (packed) t = okey[i];
+      else t = tile_key(ovf_in[i].v[0], ovf_in[i].v[1], ovf_in[i].v[2], g);
+      atomicAdd(&count[t], 1u);
+    }
+    return;
+  }
+  const int b = blockIdx.x / chunks_per_bucket, jc = blockIdx.x - b * chunks_per_bucket;
+  const uint32_t nb_ = min(bcnt[b], cap), c0 = (uint32_t)jc * REGION_CHUNK;
+  if (c0 >= nb_) return;
+  const uint32_t c1 = min(nb_, c0 + REGION_CHUNK);
+  const int wv = threadIdx.x >> 6, klo = b << (3 * g.ls);
+  hist[wv][threadIdx.x & 63] = 0u;
+  const int64_t o = (int64_t)b * cap;
+  constexpr int U = 4;  // independent loads per trip, indices clamped to the last record
+  for (uint32_t i0 = c0 + threadIdx.x; i0 < c1; i0 += 1024u * U) {
+    int t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t i = min(i0 + 1024u * u, c1 - 1u);
+      if (packed) {
+        t[u] = rkey[o + i];
+      } else {
+        const Rec<RS> r = region[o + i];
+        t[u] = tile_key(r.v[0], r.v[1], r.v[2], g);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + 1024u * u < c1) atomicAdd(&hist[wv][t[u] - klo], 1u);
+  }
+  __syncthreads();
+  if (threadIdx.x < 64u && (int)threadIdx.x < 1 << (3 * g.ls)) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) c += hist[k][threadIdx.x];
+    if (c) atomicAdd(&count[klo + threadIdx.x], c);
+  }
 }
 
 // Second counting-sort step over the bucket regions: workgroup (b, j) sorts
@@ -1530,8 +1652,8 @@ static cnpc_status sort_and_paint(const cnpc_mesh_desc* d, const uint32_t* pos, 
     kt_end(CNPC_KT_SORT, s);
     CNPC_HIP(hipGetLastError());
   }
-  const int per_bucket = 1 << (3 * g.ls);
-  hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, count, L.ntiles, per_bucket, start, cursor, bcur);
+  hipLaunchKernelGGL((L.ntiles <= 4096 ? k_tile_scan<1> : k_tile_scan<4>), dim3(1), dim3(1024), 0, s, count,
+                     L.ntiles, 3 * g.ls, start, cursor, bcur);
   CNPC_HIP(hipGetLastError());
   const bool pack = packs_records(sizeof(T) == 4, RS, g.shift);  // records of the FP32 painter
   if (L.nbuckets > 1) {
@@ -1549,6 +1671,8 @@ static cnpc_status sort_and_paint(const cnpc_mesh_desc* d, const uint32_t* pos, 
 // Bucket-pass shape: CNPC_TUNE_BUCKET 0 (default) 1024 threads; unweighted
 // catalogs with the l = 0 sums 8 particles per thread on at most 256
 // workgroups (one per CU: 130 KB of LDS), with Y_lm sums 4 on at most 512;
+// fewer per thread where such chunks would fill less than 96 CUs (4 up to
+// 7.9e5 particles, 2 up to 2.0e5);
 // weighted catalogs 2 on at most 512.  1: 1024 threads, 2 particles, next
 // chunk prefetched; 2: 512 threads, 4 particles, prefetched; 3: 1024 threads,
 // 4 particles on at most 512 workgroups.  The prefetching forms exist for
@@ -1558,14 +1682,15 @@ struct BucketShape {
   bool pf;
   int maxblk;  // persistent workgroups at most
 };
-static BucketShape bucket_shape(int rs, int lmax) {
+static BucketShape bucket_shape(int rs, int lmax, int64_t n) {
   const int v = tune_value(CNPC_TUNE_BUCKET);
   if (rs == 3 && (lmax == 0 || lmax >= 4)) {
     if (v == 1) return {1024, 2, true, BUCKET_BLOCKS_MAX};
     if (v == 2) return {512, 4, true, BUCKET_BLOCKS_MAX};
   }
   if (rs == 4) return {BUCKET_NT, 2, false, BUCKET_BLOCKS_MAX};
-  if (v == 3 || lmax > 0) return {BUCKET_NT, 4, false, BUCKET_BLOCKS_MAX};
+  if (n <= (int64_t)BUCKET_NT * 2 * 96) return {BUCKET_NT, 2, false, BUCKET_BLOCKS_MAX};
+  if (v == 3 || lmax > 0 || n <= (int64_t)BUCKET_NT * 8 * 96) return {BUCKET_NT, 4, false, BUCKET_BLOCKS_MAX};
   return {BUCKET_NT, 8, false, BUCKET_BLOCKS_MAX / 2};
 }
 
@@ -1592,6 +1717,11 @@ static void launch_bucket_pass(const BucketShape& b, unsigned nblk, size_t lds, 
                            n, sa, ba, region, ovf_out);
         return;
       }
+    }
+    if (b.per == 2) {
+      hipLaunchKernelGGL((k_bucket_pass<3, 2, BUCKET_NT, LMAX, false>), dim3(nblk), dim3(BUCKET_NT), lds, s, pos, w, n,
+                         sa, ba, region, ovf_out);
+      return;
     }
     hipLaunchKernelGGL((k_bucket_pass<3, 4, BUCKET_NT, LMAX, false>), dim3(nblk), dim3(BUCKET_NT), lds, s, pos, w, n,
                        sa, ba, region, ovf_out);
@@ -1621,7 +1751,7 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   // l = 0 sums
   const bool split_sums = sums_lmax >= 2 && tune_value(CNPC_TUNE_SORT_FUSED) == 2;
   const int lm = split_sums ? 0 : (sums_lmax >= 4 ? 4 : (sums_lmax >= 2 ? 2 : 0));
-  BucketShape bs = bucket_shape(RS, lm);
+  BucketShape bs = bucket_shape(RS, lm, n);
   const int ltiles = L.ntiles <= LDS_TILES_MAX ? L.ntiles : 0;
   const bool pack = packs_records(sizeof(T) == 4, RS, g.shift);  // records of the FP32 painter
   const bool packb = pack && L.ntiles <= 65536;                  // bucket records packed too
@@ -1666,16 +1796,25 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   kt_end(CNPC_KT_SORT, s);
   CNPC_HIP(hipGetLastError());
   const int per_bucket = 1 << (3 * g.ls);
+  if (ltiles == 0) {
+    const int rcpb = (int)((cap + REGION_CHUNK - 1) / REGION_CHUNK);
+    kt_begin(CNPC_KT_SORT, s);
+    hipLaunchKernelGGL((k_region_count<RS>), dim3((unsigned)(L.nbuckets * rcpb + OVF_BLOCKS)), dim3(1024), 0, s, region,
+                       ba.rkey, ovf_rec, ba.okey, bcnt, bcnt + L.nbuckets, cap, rcpb, L.nbuckets, g, packb, count);
+    kt_end(CNPC_KT_SORT, s);
+    CNPC_HIP(hipGetLastError());
+  }
   if (split_sums) {
     CountArgs none;
     none.ntiles = 0;
     none.count = nullptr;
     CNPC_TRY(sums_counted(d, pos, w, n, sums_lmax, sums, partial, none, s));
-    hipLaunchKernelGGL(k_tile_scan, dim3(1), dim3(1024), 0, s, count, L.ntiles, per_bucket, start, cursor, bcur);
+    hipLaunchKernelGGL((L.ntiles <= 4096 ? k_tile_scan<1> : k_tile_scan<4>), dim3(1), dim3(1024), 0, s, count,
+                     L.ntiles, 3 * g.ls, start, cursor, bcur);
   } else {
     // tile scan and the column sums of the bucket pass's partials in one launch
-    hipLaunchKernelGGL(k_tile_scan_sums, dim3(1 + CNPC_SUMS_LEN), dim3(1024), 0, s, count, L.ntiles, per_bucket,
-                       start, cursor, bcur, partial, (int)nblk, sums);
+    hipLaunchKernelGGL((L.ntiles <= 4096 ? k_tile_scan_sums<1> : k_tile_scan_sums<4>), dim3(1 + CNPC_SUMS_LEN),
+                       dim3(1024), 0, s, count, L.ntiles, start, cursor, partial, (int)nblk, sums);
   }
   CNPC_HIP(hipGetLastError());
   // tile pass: one workgroup per region chunk, then OVF_BLOCKS over the overflow
@@ -1722,13 +1861,14 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
 }
 
 // fused: sums_lmax >= 0 selects the fused bucket pass (catalog sums into
-// gs / rs, norms formed after both catalogs); counted: tile counts already taken.
+// gs / rs, and with form_norms the norms after both catalogs); counted: tile
+// counts already taken.
 template <typename T>
 static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const float* gw,
                            int64_t ngal, const uint32_t* rpos, const float* rw, int64_t nran,
                            const double* norms, T* delta, T* noise, unsigned char* ws,
                            const PaintLayout& L, bool counted, hipStream_t s, int sums_lmax = -1,
-                           double* gs = nullptr, double* rs = nullptr, bool fold = true) {
+                           double* gs = nullptr, double* rs = nullptr, bool fold = true, bool form_norms = true) {
   const bool weighted = (gw != nullptr) || (rw != nullptr);
   const uint32_t* cpos[2] = {gpos, rpos};
   const float* cw[2] = {gw, rw};
@@ -1751,7 +1891,7 @@ static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const 
     else
       CNPC_TRY((sort_and_paint<T, 3>(d, cpos[c], nullptr, cn[c], c, weighted, counted, ws, L, s)));
   }
-  if (sums_lmax >= 0) CNPC_TRY(launch_norms(d, gs, rs, ngal, const_cast<double*>(norms), s));
+  if (sums_lmax >= 0 && form_norms) CNPC_TRY(launch_norms(d, gs, rs, ngal, const_cast<double*>(norms), s));
   if (!fold) return CNPC_OK;
   const int z2 = L.nt >= 2 ? 2 : 1;
   const int64_t nb = (int64_t)L.nphase * L.nt * L.nt * (L.nt / z2);
@@ -1773,11 +1913,16 @@ cnpc_status launch_paint(const cnpc_mesh_desc* d, const uint32_t* gpos, const fl
     return CNPC_EWORKSPACE;
   }
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
+  // several buckets: the bucket pass (one read of the catalog for the tile
+  // counts and the first sort step; its l = 0 sums are not used here), else
+  // the tile count in a read of its own
+  const int lm = L.nbuckets > 1 && tune_value(CNPC_TUNE_SORT_FUSED) != 1 ? 0 : -1;
+  double* sums = reinterpret_cast<double*>(w + L.off_sums);
   if (d->dtype == CNPC_F64)
     return paint_t<double>(d, gpos, gw, ngal, rpos, rw, nran, norms, (double*)delta, (double*)noise, w,
-                           L, false, s);
+                           L, false, s, lm, sums, sums + CNPC_SUMS_LEN, true, false);
   return paint_t<float>(d, gpos, gw, ngal, rpos, rw, nran, norms, (float*)delta, (float*)noise, w, L,
-                        false, s);
+                        false, s, lm, sums, sums + CNPC_SUMS_LEN, true, false);
 }
 
 bool has_fold_zr2c(const cnpc_mesh_desc* d) {

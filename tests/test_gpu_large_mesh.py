@@ -1,0 +1,59 @@
+"""Painting on meshes of more tiles than a workgroup counts in LDS (512^3).
+
+The tile histogram then comes from the bucket-sorted records instead of the
+catalog; the meshes are integer sums, so they equal those of the sort with a
+histogram pass of its own (CNPC_TUNE_SORT_FUSED 1, which is pinned to the oracle
+on smaller meshes) bit for bit, for uniform catalogs and for clustered ones
+whose records overflow their bucket regions.
+"""
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # the marker deselects these on CPU runs
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2605_04864_amd as cn  # noqa: E402
+from paper_2605_04864_amd import _lib as L  # noqa: E402
+from paper_2605_04864_amd import pipeline as pl  # noqa: E402
+
+
+def _catalog(n, clustered, seed):
+    rng = np.random.default_rng(seed)
+    p = rng.integers(0, 1 << 32, (3, n), dtype=np.uint64)
+    if clustered:  # three quarters of the particles in one bucket's corner of the box
+        p[:, : 3 * n // 4] >>= 4
+    w = rng.uniform(0.5, 1.5, n).astype(np.float32)
+    return torch.from_numpy(p.astype(np.uint32)).cuda(), torch.from_numpy(w).cuda()
+
+
+@pytest.mark.parametrize("clustered", [False, True])
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("dtype", [L.F32, L.F64])
+def test_paint_512_matches_histogram_pass(dtype, weighted, clustered):
+    d = cn.mesh_desc(512, 2000.0, assign=L.TSC, interlace=True, dtype=dtype)
+    g, gw = _catalog(40_001, clustered, 5)
+    r, rw = _catalog(400_003, clustered, 6)
+    if not weighted:
+        gw = rw = None
+    sc = pl.Scratch()
+    out = {}
+    for knob in (1, 0):
+        L.check(L.lib.cnpc_tune_set(L.TUNE["sort_fused"][0], knob))
+        try:
+            norms, delta, noise, gs, rs = pl.paint_fkp(d, g, r, gw, rw, scratch=sc)
+            delta2, noise2 = pl.paint(d, g, r, norms, gw, rw, scratch=sc)
+            torch.cuda.synchronize()
+        finally:
+            L.check(L.lib.cnpc_tune_set(L.TUNE["sort_fused"][0], 0))
+        assert torch.equal(delta, delta2) and torch.equal(noise, noise2)
+        out[knob] = (norms, delta, noise)
+    # the catalog sums run in another order: alpha to a few ulp, and with it the meshes
+    tol = 1e-13 if dtype == L.F64 else 2.0 ** -22
+    for a, b in zip(out[0], out[1]):
+        scale = float(b.abs().max())
+        assert float((a - b).abs().max()) <= tol * scale
