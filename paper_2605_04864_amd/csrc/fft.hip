@@ -221,6 +221,76 @@ __global__ void __launch_bounds__(256) k_zpass_c2r_rr(const cx<T>* in, T* out, i
   }
 }
 
+// N = 64 .. 512: a group of L = N / 8 lanes per row pair (row_fft_g); same
+// layouts and semantics as k_zpass_r2c / k_zpass_c2r.  Both are HBM streams:
+// 8 values per lane leave the registers to several wavefronts per SIMD, and
+// the groups never wait for each other.  2 x 512^3 FP32: r2c 803 us with LDS
+// Stockham rows before, 365 here; c2r 672 us with 16 lanes x 32 values before,
+// 395 here (5.4 to 5.9 TB/s, a plain copy reaches 6.2).  14 x 128^3 FP64, r2c
+// to kz < 32: 131 -> 74 us.  The N = R^2 passes (64, 256) run at the copy rate
+// with R lanes (FP64 256^3: 89 us for 536 MB) and stay.
+template <typename T, int N>
+__global__ void __launch_bounds__(256) k_zpass_r2c_g(const T* __restrict__ in, cx<T>* __restrict__ out,
+                                                     int64_t npairs, int kz_keep) {
+  constexpr int L = N / 8, GR = 256 / L;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* tw = reinterpret_cast<cx<T>*>(smem_raw);
+  load_twiddles<T, N, -1>(tw);
+  const int grp = threadIdx.x / L, t = threadIdx.x % L;
+  cx<T>* buf = tw + N + grp * group_lds<N>;
+  const int64_t q = (int64_t)blockIdx.x * GR + grp;
+  const T* r0 = in + 2 * min(q, npairs - 1) * (int64_t)N + t;
+  cx<T> v[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) v[r] = cx<T>{r0[L * r], r0[N + L * r]};
+  __syncthreads();  // twiddles
+  row_fft_g<T, N, -1>(v, t, buf, tw);
+  cx<T>* o = out + 2 * q * (int64_t)kz_keep + t;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (L * i < kz_keep) {
+      const cx<T> zm = cconj(group_mirror<T, N>(v, t, i));
+      if (q < npairs && t + L * i < kz_keep) {
+        const cx<T> dd = csub(v[i], zm);
+        o[L * i] = cscale(cadd(v[i], zm), T(0.5));
+        o[kz_keep + L * i] = cx<T>{T(0.5) * dd.y, T(-0.5) * dd.x};
+      }
+    }
+  }
+}
+
+template <typename T, int N>
+__global__ void __launch_bounds__(256) k_zpass_c2r_g(const cx<T>* in, T* out, int64_t npairs, int kz_in) {
+  constexpr int L = N / 8, GR = 256 / L, H = N / 2;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* tw = reinterpret_cast<cx<T>*>(smem_raw);
+  load_twiddles<T, N, 1>(tw);
+  const int grp = threadIdx.x / L, t = threadIdx.x % L;
+  cx<T>* buf = tw + N + grp * group_lds<N>;
+  const int64_t q = (int64_t)blockIdx.x * GR + grp;
+  const cx<T>* r0 = in + 2 * min(q, npairs - 1) * (int64_t)kz_in;
+  cx<T> v[8];
+  // clamped straight-line loads; kz >= kz_in and the Nyquist term are zero
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const int k = t + L * r, kk = k < H ? k : N - k;
+    const int kc = min(kk, kz_in - 1);
+    const cx<T> a = r0[kc], b = r0[kz_in + kc];
+    const cx<T> z = k < H ? cx<T>{a.x - b.y, a.y + b.x} : cx<T>{a.x + b.y, b.x - a.y};
+    v[r] = kk < kz_in ? z : cx<T>{T(0), T(0)};
+  }
+  __syncthreads();  // twiddles
+  row_fft_g<T, N, 1>(v, t, buf, tw);
+  if (q < npairs) {
+    T* o = out + 2 * q * (int64_t)N + t;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      o[L * i] = v[i].x;
+      o[N + L * i] = v[i].y;
+    }
+  }
+}
+
 // ---------------------------------------------------------- column pass --
 // For each plane p and each tile of W consecutive columns: transform along the
 // row index (length N).  Input rows: all N (band_in == 0) or the 2*band_in band
@@ -545,10 +615,23 @@ template cnpc_status xpass_interlace<double>(int, const cx<double>*, cx<double>*
 // ------------------------------------------------------------- launchers --
 // side R of the register passes for N = R^2 (0: LDS Stockham passes)
 constexpr int rr_radix(int n) { return n == 64 ? 8 : n == 256 ? 16 : 0; }
+// R1 of the N = R1 (2 R1) register passes (0: none)
+constexpr int q_radix(int n) { return n == 128 ? 8 : n == 512 ? 16 : 0; }
 
 template <typename T, int N>
 static cnpc_status zr2c_n(const T* in, cx<T>* out, int64_t nrows, int kz, hipStream_t s) {
   const int64_t npairs = nrows / 2;
+  // N = 128, 512 (no square of a radix): the group kernels
+  if constexpr (q_radix(N) > 0) if (fft_register_passes()) {
+    constexpr int GR = 2048 / N;
+    const size_t lds = sizeof(cx<T>) * (N + (size_t)GR * group_lds<N>);
+    kt_begin(CNPC_KT_ZR2C, s);
+    hipLaunchKernelGGL((k_zpass_r2c_g<T, N>), dim3((unsigned)((npairs + GR - 1) / GR)), dim3(256), lds, s, in, out,
+                       npairs, kz);
+    kt_end(CNPC_KT_ZR2C, s);
+    CNPC_HIP(hipGetLastError());
+    return CNPC_OK;
+  }
   constexpr int R = rr_radix(N);
   if constexpr (R > 0) if (fft_register_passes()) {
     constexpr int GR = 256 / R;
@@ -571,14 +654,21 @@ static cnpc_status zr2c_n(const T* in, cx<T>* out, int64_t nrows, int kz, hipStr
   return CNPC_OK;
 }
 
-// R1 of the N = R1 (2 R1) register passes (0: none)
-constexpr int q_radix(int n) { return n == 128 ? 8 : n == 512 ? 16 : 0; }
-
 template <typename T, int N>
 static cnpc_status zc2r_n(const cx<T>* in, T* out, int64_t nrows, int kz, hipStream_t s) {
   const int64_t npairs = nrows / 2;
+  if constexpr (N == 512) if (fft_register_passes()) {
+    constexpr int GR = 2048 / N;
+    const size_t lds = sizeof(cx<T>) * (N + (size_t)GR * group_lds<N>);
+    kt_begin(CNPC_KT_ZC2R, s);
+    hipLaunchKernelGGL((k_zpass_c2r_g<T, N>), dim3((unsigned)((npairs + GR - 1) / GR)), dim3(256), lds, s, in, out,
+                       npairs, kz);
+    kt_end(CNPC_KT_ZC2R, s);
+    CNPC_HIP(hipGetLastError());
+    return CNPC_OK;
+  }
   constexpr int R1 = q_radix(N);
-  if constexpr (R1 > 0) if (fft_register_passes()) {
+  if constexpr (R1 > 0 && N != 512) if (fft_register_passes()) {
     constexpr int R2 = 2 * R1, GR = 256 / R1;
     const size_t lds = sizeof(cx<T>) * (N + (size_t)GR * R2 * (R1 + 1));
     kt_begin(CNPC_KT_ZC2R, s);

@@ -225,6 +225,70 @@ __device__ __forceinline__ void row_fft_q(cx<T>* v, int rank, cx<T>* buf, const 
   for (int i = 0; i < Q; ++i) dft_reg<T, R1, DIR>(v + i * R1);
 }
 
+// Length N = 64 .. 512 transform of one sequence by a group of L = N / 8 lanes
+// of one wavefront: on entry lane t holds x[t + L r] in v[r], on exit X[t + L i]
+// in v[i].  Radix-8 Stockham stages and a last stage of radix N / 64, with an
+// exchange through the group's own LDS buffer (group_lds<N> elements, one of
+// padding per 8 against bank conflicts) between two stages, ordered by
+// wavefront-level syncs only.  8 values per lane keep FP64 sequences in
+// registers with several wavefronts per SIMD, and a whole sequence needs no
+// workgroup barrier.  tw: the N-entry table W_N^t.
+template <int N>
+constexpr int group_lds = N + N / 8;
+
+template <typename T, int N, int DIR>
+__device__ __forceinline__ void row_fft_g(cx<T>* v, int t, cx<T>* buf, const cx<T>* tw) {
+  constexpr int L = N / 8, Q = N / 64;  // Q: radix of the last stage (1: none)
+  static_assert(N == 64 || N == 128 || N == 256 || N == 512, "group transforms: 64 .. 512");
+  dft8<T, DIR>(v);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) buf[9 * t + r] = v[r];  // element 8 t + r
+  wave_lds_sync();
+  const int k = t & 7;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const int e = t + r * L;
+    const cx<T> a = buf[e + (e >> 3)];
+    v[r] = r == 0 ? a : cmul(a, tw[r * k * (N / 64)]);
+  }
+  dft8<T, DIR>(v);
+  if constexpr (Q > 1) {
+    wave_lds_sync();
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int e = (t - k) * 8 + k + 8 * r;
+      buf[e + (e >> 3)] = v[r];
+    }
+    wave_lds_sync();
+    // 8 / Q butterflies of radix Q: j = t + L q, inputs j + 64 r, outputs X[j + 64 r]
+#pragma unroll
+    for (int q = 0; q < 8 / Q; ++q) {
+      cx<T> u[Q];
+#pragma unroll
+      for (int r = 0; r < Q; ++r) {
+        const int j = t + L * q, e = j + 64 * r;
+        const cx<T> a = buf[e + (e >> 3)];
+        u[r] = r == 0 ? a : cmul(a, tw[r * j]);
+      }
+      dft_reg<T, Q, DIR>(u);
+#pragma unroll
+      for (int r = 0; r < Q; ++r) v[q + (8 / Q) * r] = u[r];
+    }
+  }
+  wave_lds_sync();  // the buffer may be written again
+}
+
+// Z[N - k] for k = t + L i of a sequence that row_fft_g left in v (lane L - t,
+// register 7 - i; lane 0 holds its own partners)
+template <typename T, int N>
+__device__ __forceinline__ cx<T> group_mirror(const cx<T>* v, int t, int i) {
+  constexpr int L = N / 8;
+  const cx<T> a = v[7 - i];
+  const int src = (L - t) & (L - 1);
+  const cx<T> sh = {__shfl(a.x, src, L), __shfl(a.y, src, L)};
+  return t ? sh : v[(8 - i) & 7];
+}
+
 // Twiddle table tw[t] = exp(DIR 2 pi i t / N) into LDS.
 template <typename T, int N, int DIR>
 __device__ __forceinline__ void load_twiddles(cx<T>* tw) {

@@ -7,6 +7,8 @@ on smaller meshes) bit for bit, for uniform catalogs and for clustered ones
 whose records overflow their bucket regions.
 """
 
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -57,3 +59,33 @@ def test_paint_512_matches_histogram_pass(dtype, weighted, clustered):
     for a, b in zip(out[0], out[1]):
         scale = float(b.abs().max())
         assert float((a - b).abs().max()) <= tol * scale
+
+
+@pytest.mark.parametrize("dtype,band", [(L.F32, 0), (L.F64, 128)])
+def test_fft_512_both_directions(dtype, band):
+    """512^3 transforms (z passes of one wavefront per row pair) against numpy, the
+    full half spectrum and a band of two kz per lane."""
+    n, m = 512, band or 256
+    d = cn.mesh_desc(n, 100.0, dtype=dtype)
+    tdt = torch.float64 if dtype == L.F64 else torch.float32
+    x = np.random.default_rng(band).normal(size=(n, n, n)).astype(np.float32)
+    ref = np.fft.rfftn(x.astype(np.float64))
+    idx = np.r_[0:m, n - m:n] if band else np.arange(n)
+    ref = np.ascontiguousarray(ref[:, :, :m] if not band else ref[np.ix_(idx, idx, range(m))])
+    xt = torch.from_numpy(x).to(tdt).cuda()
+    spec = torch.empty(ref.shape + (2,), dtype=tdt, device="cuda")
+    ws = torch.empty(max(256, L.lib.cnpc_fft_workspace_size(C.byref(d), 1, band)), dtype=torch.uint8, device="cuda")
+    L.check(L.lib.cnpc_fft_r2c(C.byref(d), 1, band, L.ptr(xt), L.ptr(spec), L.ptr(ws), ws.numel(), L.stream_handle()))
+    got = torch.view_as_complex(spec.double()).cpu().numpy()
+    tol = 1e-10 if dtype == L.F64 else 1e-5
+    assert np.max(np.abs(got - ref)) < tol * np.max(np.abs(ref))
+    # back: the band's modes alone, the Nyquist / n = -m rows empty
+    ref[m if band else n // 2] = 0
+    ref[:, m if band else n // 2] = 0
+    full = np.zeros((n, n, n // 2 + 1), dtype=np.complex128)
+    full[np.ix_(idx, idx, range(m))] = ref
+    want = np.fft.irfftn(full, s=(n, n, n)) * float(n) ** 3
+    st = torch.view_as_real(torch.from_numpy(ref)).to(tdt).cuda().contiguous()
+    mesh = torch.empty((n, n, n), dtype=tdt, device="cuda")
+    L.check(L.lib.cnpc_fft_c2r(C.byref(d), 1, band, L.ptr(st), L.ptr(mesh), L.ptr(ws), ws.numel(), L.stream_handle()))
+    assert np.max(np.abs(mesh.double().cpu().numpy() - want)) < tol * np.max(np.abs(want))
