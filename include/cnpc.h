@@ -557,8 +557,9 @@ cnpc_status cnpc_ktimer_stop(double* ms_per_class, int64_t* launches_per_class);
  *                          x 2 with the next chunk loaded during the current
  *                          one; 2: 512 x 4, likewise; 3: 1024 x 4 on two
  *                          workgroups per CU).
- *   CNPC_TUNE_YLM_BASIS    FP32 Y_lm z passes of bands kz < 4 R (N = R^2 of
- *                          the register passes): 0 (default) transforms
+ *   CNPC_TUNE_YLM_BASIS    Y_lm z passes of N = 64 .. 512 with register passes
+ *                          (FP32 of 64, 256: bands kz < 4 sqrt(N)): 0
+ *                          (default) transforms
  *                          delta R^-L r_z^j, j = 0..L, per parity class of l
  *                          (L its largest l) and forms every field of the
  *                          class from these L + 1 spectra (5 for l = 2, 4);

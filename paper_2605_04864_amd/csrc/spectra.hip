@@ -760,6 +760,186 @@ __global__ void __launch_bounds__(256) k_colpass_ylm_rr(const cx<T>* __restrict_
   }
 }
 
+// ------------------------------------ z pass by powers of r_z, lane groups --
+// The fields of k_zpass_ylm_basis from the same identity (delta R^-L r_z^j,
+// j = 0..L, one set per parity class of l), for every N = 64 .. 512 and both
+// types: a group of N / 8 lanes per row pair (row_fft_g), 8 values per lane,
+// so that FP64 rows and rows of 512 keep all bases of the kept kz in registers
+// (kz_keep <= K2M N / 8).  The per-row coefficients of the fields are formed
+// once per workgroup in LDS.  What bounds it: the FP64 row transforms and the
+// writes of the fields (2l + 1 band planes per l); one read of delta.
+// 256^3 FP64, l = 2, 4, M = 32: 998 us with a transform per field
+// (k_zpass_ylm_rr, 14 of them) before, 176 us here; 512^3 FP32, l = 2,
+// M = 128: 2028 us with LDS Stockham rows (k_zpass_ylm) before, 487 us here.
+struct RowPoly {  // a field's row polynomial: coefficients of r_z^(odd + 2 i)
+  double e[3];
+};
+
+__device__ __forceinline__ RowPoly row_poly(int l, int m, int part, int L, double rx, double ry) {
+  RowPoly p;
+  const double rho = rx * rx + ry * ry;
+  const SolidQ q = solid_coef(l, m);
+  const ZPoly<double> a = zpoly<double>(q, rho, cpow_part<double>(rx, ry, m, part));
+  p.e[0] = a.c0;
+  p.e[1] = a.c2;
+  p.e[2] = a.c4;
+  for (int k = l; k < L; k += 2) {  // times rho^2 + r_z^2 (the degree stays <= 4)
+    p.e[2] = p.e[2] * rho + p.e[1];
+    p.e[1] = p.e[1] * rho + p.e[0];
+    p.e[0] = p.e[0] * rho;
+  }
+  return p;
+}
+
+// basis J of the row pair: transform of (d0, d1) r_z^J, split per row at the
+// kept kz = t + L i (i < K2M)
+template <typename T, int N, int K2M, int J>
+__device__ __forceinline__ void zbasis_g(const T* d0, const T* d1, T rz0, T dz, int t, cx<T>* buf, const cx<T>* tw,
+                                         cx<T>* g0, cx<T>* g1) {
+  cx<T> v[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    T za = rz0 + T(r) * dz;
+    asm volatile("" : "+v"(za));  // recomputed per basis, not held in registers
+    const T w = zpow<T, J>(za);
+    v[r] = J == 0 ? cx<T>{d0[r], d1[r]} : cx<T>{d0[r] * w, d1[r] * w};
+  }
+  row_fft_g<T, N, -1>(v, t, buf, tw);
+#pragma unroll
+  for (int i = 0; i < K2M; ++i) {
+    const cx<T> zm = cconj(group_mirror<T, N>(v, t, i));
+    const cx<T> dd = csub(v[i], zm);
+    g0[i] = cscale(cadd(v[i], zm), T(0.5));
+    g1[i] = cx<T>{T(0.5) * dd.y, T(-0.5) * dd.x};
+  }
+}
+
+template <typename T, int N, int K2M>
+__global__ void __launch_bounds__(256, K2M == 4 && sizeof(T) == 8 ? 1 : 2)
+    k_zpass_ylm_g(const T* __restrict__ delta, cx<T>* __restrict__ out, FieldTable ft, int kz_keep,
+                  int64_t fstride, Geo g) {
+  constexpr int L8 = N / 8, GR = 256 / L8;  // lanes per row pair, row pairs per workgroup
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* tw = reinterpret_cast<cx<T>*>(smem_raw);
+  cx<T>* bufs = tw + N;
+  T* ecf = reinterpret_cast<T*>(bufs + GR * group_lds<N>);  // [nf][2 GR][3]
+  load_twiddles<T, N, -1>(tw);
+  const int grp = threadIdx.x / L8, t = threadIdx.x % L8;
+  cx<T>* buf = bufs + grp * group_lds<N>;
+  // GR divides N / 2: the workgroup's row pairs share ix
+  const int q0 = blockIdx.x * GR;
+  const int ix = q0 / (N / 2), iyb = 2 * (q0 - ix * (N / 2)), iy0 = iyb + 2 * grp;
+  int Lc[2] = {-1, -1};  // largest l of each parity
+  for (int f = 0; f < ft.nf; ++f) {
+    const int l = ft.ell[f];
+    if (l > Lc[l & 1]) Lc[l & 1] = l;
+  }
+  for (int i = threadIdx.x; i < ft.nf * 2 * GR; i += 256) {
+    const int f = i / (2 * GR), row = i - f * 2 * GR;
+    const int l = ft.ell[f], m = ft.m[f], p = ft.part[f];
+    if (g.global_los) {
+      ecf[3 * i] = ylm_one<T>(l, m, p, T(g.los[0]), T(g.los[1]), T(g.los[2]));
+      ecf[3 * i + 1] = ecf[3 * i + 2] = T(0);
+    } else {
+      const RowPoly e = row_poly(l, m, p, (l & 1) ? Lc[1] : Lc[0], ix * g.h - g.obs[0], (iyb + row) * g.h - g.obs[1]);
+      ecf[3 * i] = T(e.e[0]);
+      ecf[3 * i + 1] = T(e.e[1]);
+      ecf[3 * i + 2] = T(e.e[2]);
+    }
+  }
+  const T* r0 = delta + ((int64_t)ix * N + iy0) * N + t;
+  T d0[8], d1[8];
+  int pw = 0;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    d0[r] = r0[L8 * r];
+    d1[r] = r0[N + L8 * r];
+  }
+  const T rz0 = T(t * g.h - g.obs[2]), dz = T(L8 * g.h);
+  const T rx = T(ix * g.h - g.obs[0]);
+  const T ry0 = T(iy0 * g.h - g.obs[1]), ry1 = T((iy0 + 1) * g.h - g.obs[1]);
+  const T rho0 = rx * rx + ry0 * ry0, rho1 = rx * rx + ry1 * ry1;
+  __syncthreads();  // twiddles, coefficients
+  cx<T>* orow = out + ((int64_t)ix * N + iy0) * kz_keep + t;
+  cx<T> g0[5][K2M], g1[5][K2M];
+#pragma unroll
+  for (int j = 0; j < 5; ++j)
+#pragma unroll
+    for (int i = 0; i < K2M; ++i) g0[j][i] = g1[j][i] = cx<T>{T(0), T(0)};
+  bool have = false;  // a global line of sight needs G_0 once
+  for (int par = 1; par >= 0; --par) {  // odd l, then even l
+    const int L = Lc[par];
+    if (L < 0) continue;
+    if (!g.global_los) {
+      if (L != pw) {
+        if (L < pw) {
+#pragma unroll
+          for (int r = 0; r < 8; ++r) {
+            d0[r] = r0[L8 * r];
+            d1[r] = r0[N + L8 * r];
+          }
+          pw = 0;
+        }
+        switch (L - pw) {
+          case 1: scale_rows<T, 8, 1>(d0, d1, rz0, dz, rho0, rho1); break;
+          case 2: scale_rows<T, 8, 2>(d0, d1, rz0, dz, rho0, rho1); break;
+          case 3: scale_rows<T, 8, 3>(d0, d1, rz0, dz, rho0, rho1); break;
+          case 4: scale_rows<T, 8, 4>(d0, d1, rz0, dz, rho0, rho1); break;
+          default: break;
+        }
+        pw = L;
+      }
+      zbasis_g<T, N, K2M, 0>(d0, d1, rz0, dz, t, buf, tw, g0[0], g1[0]);
+      if (L >= 1) zbasis_g<T, N, K2M, 1>(d0, d1, rz0, dz, t, buf, tw, g0[1], g1[1]);
+      if (L >= 2) zbasis_g<T, N, K2M, 2>(d0, d1, rz0, dz, t, buf, tw, g0[2], g1[2]);
+      if (L >= 3) zbasis_g<T, N, K2M, 3>(d0, d1, rz0, dz, t, buf, tw, g0[3], g1[3]);
+      if (L >= 4) zbasis_g<T, N, K2M, 4>(d0, d1, rz0, dz, t, buf, tw, g0[4], g1[4]);
+    } else if (!have) {
+      zbasis_g<T, N, K2M, 0>(d0, d1, rz0, dz, t, buf, tw, g0[0], g1[0]);
+      have = true;
+    }
+    for (int f = 0; f < ft.nf; ++f) {
+      const int l = ft.ell[f];
+      if ((l & 1) != par) continue;
+      const bool odd = !g.global_los && ((l - ft.m[f]) & 1);
+      const T* a = ecf + 3 * (f * 2 * GR + 2 * grp);
+      const T a0 = a[0], a2 = a[1], a4 = a[2], b0 = a[3], b2 = a[4], b4 = a[5];
+      cx<T>* o = orow + (int64_t)f * fstride;
+#pragma unroll
+      for (int i = 0; i < K2M; ++i) {
+        if (t + L8 * i < kz_keep) {
+          if (odd) {
+            o[L8 * i] = zcombine<T, K2M, 1>(g0, i, a0, a2, a4);
+            o[kz_keep + L8 * i] = zcombine<T, K2M, 1>(g1, i, b0, b2, b4);
+          } else {
+            o[L8 * i] = zcombine<T, K2M, 0>(g0, i, a0, a2, a4);
+            o[kz_keep + L8 * i] = zcombine<T, K2M, 0>(g1, i, b0, b2, b4);
+          }
+        }
+      }
+    }
+  }
+}
+
+template <typename T, int N>
+static cnpc_status zylm_g(const T* delta, cx<T>* out, const FieldTable& ft, int kz, int64_t fstride, const Geo& g,
+                          hipStream_t s) {
+  constexpr int L8 = N / 8, GR = 256 / L8;
+  const size_t lds = sizeof(cx<T>) * (N + (size_t)GR * group_lds<N>) + sizeof(T) * 3 * 2 * GR * ft.nf;
+  const dim3 grid(N * (N / 2) / GR);
+  const int k2 = (kz + L8 - 1) / L8;
+  kt_begin(CNPC_KT_ZR2C, s);
+  if (k2 <= 1)
+    hipLaunchKernelGGL((k_zpass_ylm_g<T, N, 1>), grid, dim3(256), lds, s, delta, out, ft, kz, fstride, g);
+  else if (k2 == 2)
+    hipLaunchKernelGGL((k_zpass_ylm_g<T, N, 2>), grid, dim3(256), lds, s, delta, out, ft, kz, fstride, g);
+  else
+    hipLaunchKernelGGL((k_zpass_ylm_g<T, N, 4>), grid, dim3(256), lds, s, delta, out, ft, kz, fstride, g);
+  kt_end(CNPC_KT_ZR2C, s);
+  CNPC_HIP(hipGetLastError());
+  return CNPC_OK;
+}
+
 template <typename T, int R>
 static cnpc_status zylm_rr(const T* delta, cx<T>* out, const FieldTable& ft, int kz, int64_t fstride,
                            const Geo& g, hipStream_t s) {
@@ -806,9 +986,20 @@ static cnpc_status zylm_n(const T* delta, cx<T>* out, const FieldTable& ft, int 
   return CNPC_OK;
 }
 
+// z pass of the Y_lm fields: by powers of r_z in lane groups for FP64 at 64 ..
+// 512 and FP32 at 128, 512 (FP32 at 64 and 256 has the register passes of
+// zylm_rr); CNPC_TUNE_YLM_BASIS 1 takes one transform per field everywhere
 template <typename T>
 static cnpc_status zpass_ylm(int n, const T* delta, cx<T>* out, const FieldTable& ft, int kz,
                              int64_t fstride, const Geo& g, hipStream_t s) {
+  if (fft_register_passes() && tune_value(CNPC_TUNE_YLM_BASIS) != 1) {
+    if (n == 128) return zylm_g<T, 128>(delta, out, ft, kz, fstride, g, s);
+    if (n == 512) return zylm_g<T, 512>(delta, out, ft, kz, fstride, g, s);
+    if constexpr (sizeof(T) == 8) {
+      if (n == 64) return zylm_g<T, 64>(delta, out, ft, kz, fstride, g, s);
+      if (n == 256) return zylm_g<T, 256>(delta, out, ft, kz, fstride, g, s);
+    }
+  }
   switch (n) {
     case 16: return zylm_rr<T, 4>(delta, out, ft, kz, fstride, g, s);
     case 32: return zylm_n<T, 32>(delta, out, ft, kz, fstride, g, s);

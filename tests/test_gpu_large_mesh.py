@@ -22,6 +22,7 @@ if not torch.cuda.is_available():  # the marker deselects these on CPU runs
 import paper_2605_04864_amd as cn  # noqa: E402
 from paper_2605_04864_amd import _lib as L  # noqa: E402
 from paper_2605_04864_amd import pipeline as pl  # noqa: E402
+import test_gpu_parity as P  # noqa: E402
 
 
 def _catalog(n, clustered, seed):
@@ -84,8 +85,35 @@ def test_fft_512_both_directions(dtype, band):
     ref[:, m if band else n // 2] = 0
     full = np.zeros((n, n, n // 2 + 1), dtype=np.complex128)
     full[np.ix_(idx, idx, range(m))] = ref
-    want = np.fft.irfftn(full, s=(n, n, n)) * float(n) ** 3
+    want = np.fft.irfftn(full, s=(n, n, n), axes=(0, 1, 2)) * float(n) ** 3
     st = torch.view_as_real(torch.from_numpy(ref)).to(tdt).cuda().contiguous()
     mesh = torch.empty((n, n, n), dtype=tdt, device="cuda")
     L.check(L.lib.cnpc_fft_c2r(C.byref(d), 1, band, L.ptr(st), L.ptr(mesh), L.ptr(ws), ws.numel(), L.stream_handle()))
     assert np.max(np.abs(mesh.double().cpu().numpy() - want)) < tol * np.max(np.abs(want))
+
+
+# the z pass in lane groups: one, two and four kz per lane, odd and even l
+# together, a global line of sight
+@pytest.mark.parametrize("n,band,dtype,ells,los", [
+    (64, 8, L.F64, (1, 2, 3, 4), None), (64, 32, L.F64, (4,), None), (128, 16, L.F32, (1, 3), None),
+    (128, 64, L.F64, (2,), None), (256, 64, L.F64, (1, 2, 3, 4), None), (128, 32, L.F64, (2, 4), P.YLM_LOS)])
+def test_ylm_lane_groups(n, band, dtype, ells, los):
+    P.test_ylm_r2c_band(n, band, dtype, ells, los)
+
+
+@pytest.mark.parametrize("dtype,tol", [(L.F32, 2e-5), (L.F64, 1e-10)])
+def test_ylm_512_matches_field_transforms(dtype, tol):
+    """512^3: fields from the powers of r_z against one transform per field
+    (CNPC_TUNE_YLM_BASIS 1)."""
+    d = cn.mesh_desc(512, 2000.0, dtype=dtype)
+    x = torch.randn((512, 512, 512), dtype=torch.float64, device="cuda").to(pl._TORCH_DT[dtype])
+    out = {}
+    for knob in (0, 1):
+        L.check(L.lib.cnpc_tune_set(L.TUNE["ylm_basis"][0], knob))
+        try:
+            out[knob] = pl.ylm_spectra(d, 128, (2,), x)[2]
+            torch.cuda.synchronize()
+        finally:
+            L.check(L.lib.cnpc_tune_set(L.TUNE["ylm_basis"][0], 0))
+    for a, b in zip(out[0], out[1]):
+        assert float((a - b).abs().max()) <= tol * float(b.abs().max())
