@@ -834,6 +834,253 @@ cnpc_status contract_mfma_fp(const T* fields, int64_t npts, int nf, int nshell, 
   return reduce_blocks(partial, CONTRACT_BLOCKS * kg, (int64_t)npairs * cc.ncols, out, s);
 }
 
+// ------------------------------------------ FP64 shell-by-shell contraction --
+// C[i, j] = sum_x P_i(x) W_j(x) as a GEMM over grid points with
+// v_mfma_f64_16x16x4_f64: the sums whose pair products share one third field,
+// nb x nb outputs from nb rows and nb columns, where k_contract_mfma_fp has a
+// row per pair and one column (1 of 16 columns of its tiles at work).
+//   k_cross_mfma: W_j = c1 X_j Z1 + c2 Y_j Z2 (Sugiyama legs; a term with a
+//   null field is left out), row-major nb x nb;
+//   k_cross_mfma_sym: W_j = P_j Z (TripoSH), the triangle i <= j in
+//   lexicographic pair order, the tiles above the diagonal alone.
+// Operand layout: lane l holds row l % 16 and, of a 32-point step, the points
+// 8 u + 2 (l / 16) + {0, 1}, u < 4, one per instruction; a wavefront holds all
+// tiles, so every field is read once in total.  Bound by the field reads and
+// the FP64 matrix rate alike.
+typedef double f64x2_t __attribute__((ext_vector_type(2)));
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+// a 16-row tile's 8 values per lane of a 32-point step
+__device__ __forceinline__ void cross_load8(const double* __restrict__ p, double* v) {
+  const double2* p2 = reinterpret_cast<const double2*>(p);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const double2 d = p2[4 * u];
+    v[2 * u] = d.x;
+    v[2 * u + 1] = d.y;
+  }
+}
+
+// Loads straight from memory (a row's four lanes read 64 consecutive bytes per
+// load), W_j formed in registers, no LDS and no barrier in the loop.  128^3,
+// 20 x 20 shells, FP64: 408 us and 122 us for W in a kernel of its own before,
+// 171 us here (the fields of a 128^3 grid lie 16 MB apart; on 256^3 this access,
+// 16 fields 128 MB apart per load, reached only 1.9 TB/s, which is why the
+// symmetric form stages rows of 1 KB).
+constexpr int CROSS_BLOCKS = 512;
+template <int NTL>
+__global__ void __launch_bounds__(256, NTL >= 3 ? 1 : 2)
+    k_cross_mfma(const double* __restrict__ P, const double* __restrict__ X, const double* __restrict__ Z1, double c1,
+                 const double* __restrict__ Y, const double* __restrict__ Z2, double c2, int nb, int64_t npts,
+                 double* __restrict__ partial) {
+  __shared__ double red[256 * NTL * NTL];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = lane & 15, q = lane >> 4;
+  f64x4_t acc[NTL][NTL];
+#pragma unroll
+  for (int i = 0; i < NTL; ++i)
+#pragma unroll
+    for (int j = 0; j < NTL; ++j) acc[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  int64_t fo[NTL];  // field offset of the tile's row (rows past nb repeat the last field; not stored)
+#pragma unroll
+  for (int i = 0; i < NTL; ++i) fo[i] = (int64_t)min(i * 16 + row, nb - 1) * npts;
+  const int64_t steps = npts / 32;
+  for (int64_t st = (int64_t)blockIdx.x * 4 + wave; st < steps; st += (int64_t)gridDim.x * 4) {
+    const int64_t x = st * 32 + q * 2;
+    double a[NTL][8], w[NTL][8], z[8];
+#pragma unroll
+    for (int i = 0; i < NTL; ++i) cross_load8(P + fo[i] + x, a[i]);
+#pragma unroll
+    for (int j = 0; j < NTL; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w[j][e] = 0.0;
+    if (X) {
+      cross_load8(Z1 + x, z);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) z[e] *= c1;
+#pragma unroll
+      for (int j = 0; j < NTL; ++j) {
+        double u[8];
+        cross_load8(X + fo[j] + x, u);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[j][e] = u[e] * z[e];
+      }
+    }
+    if (Y) {
+      cross_load8(Z2 + x, z);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) z[e] *= c2;
+#pragma unroll
+      for (int j = 0; j < NTL; ++j) {
+        double u[8];
+        cross_load8(Y + fo[j] + x, u);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[j][e] += u[e] * z[e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < NTL; ++i)
+#pragma unroll
+        for (int j = 0; j < NTL; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][e], w[j][e], acc[i][j], 0, 0, 0);
+  }
+  // the four wavefronts' tiles summed through LDS in a fixed order; register v
+  // of lane l is D[4 v + l / 16][l % 16]
+  for (int k = 0; k < 4; ++k) {
+    if (wave == k) {
+#pragma unroll
+      for (int i = 0; i < NTL; ++i)
+#pragma unroll
+        for (int j = 0; j < NTL; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            double* r = red + (i * NTL + j) * 256 + (4 * v + q) * 16 + row;
+            *r = (k == 0 ? 0.0 : *r) + acc[i][j][v];
+          }
+    }
+    __syncthreads();
+  }
+  double* out = partial + (int64_t)blockIdx.x * nb * nb;
+  for (int e = threadIdx.x; e < nb * nb; e += 256) {
+    const int i = e / nb, j = e - i * nb;
+    out[e] = red[((i >> 4) * NTL + (j >> 4)) * 256 + (i & 15) * 16 + (j & 15)];
+  }
+}
+
+// Rows of 128 points of every field (1 KB of consecutive memory per wavefront
+// load) staged in LDS, the next chunk waiting in registers meanwhile; wavefront
+// w contracts points 32 w .. 32 w + 31 of the chunk.  The 2-element row padding
+// puts the 16 rows of a tile on distinct banks.  256^3, 40 shells, FP64: 9.8 ms
+// with a row per pair before, 0.99 ms here (5.6 TB/s).
+constexpr int CS_KC = 128, CS_ROW = CS_KC + 2;
+constexpr int CROSS_SYM_BLOCKS = 768;  // three workgroups per CU
+template <int NTL>
+__global__ void __launch_bounds__(256, NTL >= 4 ? 2 : 3)
+    k_cross_mfma_sym(const double* __restrict__ P, const double* __restrict__ Z, int nb, int64_t npts,
+                     double* __restrict__ partial) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* tile = reinterpret_cast<double*>(smem_raw);  // [nb + 1][CS_ROW], row nb: Z; later the wavefronts' sums
+  constexpr int NV = 4 * NTL + 1;                      // double2 per thread and chunk
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int row = lane & 15, q = lane >> 4;
+  f64x4_t acc[NTL][NTL];
+#pragma unroll
+  for (int i = 0; i < NTL; ++i)
+#pragma unroll
+    for (int j = i; j < NTL; ++j) acc[i][j] = f64x4_t{0.0, 0.0, 0.0, 0.0};
+  const double* rows[NTL];  // rows past nb repeat the last field; not stored
+#pragma unroll
+  for (int i = 0; i < NTL; ++i) rows[i] = tile + min(i * 16 + row, nb - 1) * CS_ROW + 32 * wave + 2 * q;
+  const double* zrow = tile + nb * CS_ROW + 32 * wave + 2 * q;
+  const int nv = (nb + 1) * (CS_KC / 2);  // double2 of a chunk
+  const int64_t chunks = npts / CS_KC;
+  f64x2_t pre[NV];
+  for (int64_t c = blockIdx.x; c < chunks; c += gridDim.x) {
+    const bool first = c == (int64_t)blockIdx.x;
+    if (first) {
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        const int idx = min((int)threadIdx.x + 256 * k, nv - 1), f = idx / (CS_KC / 2);
+        pre[k] = reinterpret_cast<const f64x2_t*>((f < nb ? P + (int64_t)f * npts : Z) + c * CS_KC)[idx % (CS_KC / 2)];
+      }
+    }
+    __syncthreads();  // the previous chunk is consumed
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int idx = threadIdx.x + 256 * k;
+      if (idx < nv)
+        *reinterpret_cast<f64x2_t*>(tile + (idx / (CS_KC / 2)) * CS_ROW + 2 * (idx % (CS_KC / 2))) = pre[k];
+    }
+    __syncthreads();
+    const int64_t cn = min(c + (int64_t)gridDim.x, chunks - 1);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int idx = min((int)threadIdx.x + 256 * k, nv - 1), f = idx / (CS_KC / 2);
+      pre[k] = reinterpret_cast<const f64x2_t*>((f < nb ? P + (int64_t)f * npts : Z) + cn * CS_KC)[idx % (CS_KC / 2)];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const f64x2_t z = *reinterpret_cast<const f64x2_t*>(zrow + 8 * u);
+      f64x2_t a[NTL];
+#pragma unroll
+      for (int i = 0; i < NTL; ++i) a[i] = *reinterpret_cast<const f64x2_t*>(rows[i] + 8 * u);
+#pragma unroll
+      for (int j = 0; j < NTL; ++j) {
+        const double w0 = a[j].x * z.x, w1 = a[j].y * z.y;
+#pragma unroll
+        for (int i = 0; i <= j; ++i) {
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, w0, acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, w1, acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+  }
+  double* red = tile;
+  for (int k = 0; k < 4; ++k) {
+    __syncthreads();
+    if (wave == k) {
+#pragma unroll
+      for (int i = 0; i < NTL; ++i)
+#pragma unroll
+        for (int j = i; j < NTL; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            double* r = red + (i * NTL - i * (i - 1) / 2 + (j - i)) * 256 + (4 * v + q) * 16 + row;
+            *r = (k == 0 ? 0.0 : *r) + acc[i][j][v];
+          }
+    }
+  }
+  __syncthreads();
+  double* out = partial + (int64_t)blockIdx.x * (nb * (nb + 1) / 2);
+  for (int e = threadIdx.x; e < nb * nb; e += 256) {
+    const int i = e / nb, j = e - i * nb;
+    if (j < i) continue;
+    const int ti = i >> 4, t = ti * NTL - ti * (ti - 1) / 2 + ((j >> 4) - ti);
+    out[i * nb - i * (i - 1) / 2 + (j - i)] = red[t * 256 + (i & 15) * 16 + (j & 15)];
+  }
+}
+
+template <int NTL>
+static void launch_cross_sym(const double* P, const double* Z, int nb, int64_t npts, double* partial, hipStream_t s) {
+  const size_t lds_tile = sizeof(double) * (nb + 1) * CS_ROW, lds_red = sizeof(double) * 256 * NTL * (NTL + 1) / 2;
+  hipLaunchKernelGGL((k_cross_mfma_sym<NTL>), dim3(CROSS_SYM_BLOCKS), dim3(256), lds_tile > lds_red ? lds_tile : lds_red,
+                     s, P, Z, nb, npts, partial);
+}
+
+// up to 64 shells (4 row tiles) on a grid of whole chunks (16^3 and more)
+static bool contract_cross_sym_ok(int nb, int64_t npts) { return nb <= 64 && npts % CS_KC == 0; }
+
+// out: the nb (nb + 1) / 2 sums P_i P_j Z; partial: CROSS_SYM_BLOCKS times that
+static cnpc_status contract_cross_sym(const double* P, const double* Z, int nb, int64_t npts, double* partial,
+                                      double* out, hipStream_t s) {
+  kt_begin(CNPC_KT_CONTRACT, s);
+  if (nb <= 16) launch_cross_sym<1>(P, Z, nb, npts, partial, s);
+  else if (nb <= 32) launch_cross_sym<2>(P, Z, nb, npts, partial, s);
+  else if (nb <= 48) launch_cross_sym<3>(P, Z, nb, npts, partial, s);
+  else launch_cross_sym<4>(P, Z, nb, npts, partial, s);
+  kt_end(CNPC_KT_CONTRACT, s);
+  CNPC_HIP(hipGetLastError());
+  return reduce_blocks(partial, CROSS_SYM_BLOCKS, (int64_t)nb * (nb + 1) / 2, out, s);
+}
+
+// out: nb x nb sums P_i W_j (nb <= MAX_COLS, grids of 16^3 and more); partial:
+// CROSS_BLOCKS times that
+static cnpc_status contract_cross(const double* P, const double* X, const double* Z1, double c1, const double* Y,
+                                  const double* Z2, double c2, int nb, int64_t npts, double* partial, double* out,
+                                  hipStream_t s) {
+  static_assert(MAX_COLS <= 48, "three row tiles");
+  const dim3 g(CROSS_BLOCKS), b(256);
+  kt_begin(CNPC_KT_CONTRACT, s);
+  if (nb <= 16) hipLaunchKernelGGL((k_cross_mfma<1>), g, b, 0, s, P, X, Z1, c1, Y, Z2, c2, nb, npts, partial);
+  else if (nb <= 32) hipLaunchKernelGGL((k_cross_mfma<2>), g, b, 0, s, P, X, Z1, c1, Y, Z2, c2, nb, npts, partial);
+  else hipLaunchKernelGGL((k_cross_mfma<3>), g, b, 0, s, P, X, Z1, c1, Y, Z2, c2, nb, npts, partial);
+  kt_end(CNPC_KT_CONTRACT, s);
+  CNPC_HIP(hipGetLastError());
+  return reduce_blocks(partial, CROSS_BLOCKS, (int64_t)nb * nb, out, s);
+}
+
 // --------------------------------------------------- shell-filtered c2r --
 // Half-width of the band that holds every mode of the shells below the last
 // threshold, the smallest power of two above its largest |component| (<= m).
@@ -1274,6 +1521,11 @@ void bispec_plan_destroy(cnpc_bispec_plan* P) {
 template <typename T>
 static cnpc_status contract_any(const cnpc_bispec_plan* P, const T* fields, int64_t n3, double* partial,
                                 double* out, hipStream_t s) {
+  if constexpr (sizeof(T) == 8) {
+    // TripoSH: every pair i <= j of the shells (the plan's rows, in that order) times field nb
+    if (P->est == CNPC_EST_TRIPOSH && contract_cross_sym_ok(P->nb, n3))
+      return contract_cross_sym(fields, fields + (int64_t)P->nb * n3, P->nb, n3, partial, out, s);
+  }
   if constexpr (sizeof(T) == 4) {
     if (P->prec == CNPC_PREC_BF16X3)
       return contract_mfma(fields, n3, P->nfields, P->nb, P->cc, partial, out, s, P->d_pairs, (int)P->pairs.size());

@@ -411,8 +411,10 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
   T* slotQb = slotQa + (int64_t)nb * n3;
   T* slotG = slotQb + (int64_t)nb * n3;
   T* slotH = slotG + n3;
-  hipLaunchKernelGGL((k_fill_real<T>), dim3(1024), dim3(256), 0, s, slotOne, n3, T(1));
-  CNPC_HIP(hipGetLastError());
+  if constexpr (sizeof(T) == 4) {
+    hipLaunchKernelGGL((k_fill_real<T>), dim3(1024), dim3(256), 0, s, slotOne, n3, T(1));
+    CNPC_HIP(hipGetLastError());
+  }
   const unsigned gw = (unsigned)std::min<int64_t>((n3 + 255) / 256, 8192);
   // leg field (l, m, part) of every shell into a slot, from F_0 (signal) or
   // from ones (harmonic shell indicators of the FFT-method noise)
@@ -433,6 +435,12 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
   double* accum = acc;
   auto contract_add = [&](const T* X, const T* Z1, double c1, const T* Y, const T* Z2, double c2, double coef,
                           int transpose) -> cnpc_status {
+    if constexpr (sizeof(T) == 8) {  // W formed inside the contraction (nb <= MAX_COLS shells)
+      CNPC_TRY(contract_cross(slotP, X, Z1, c1, Y, Z2, c2, nb, n3, partial, Cm, s));
+      hipLaunchKernelGGL(k_sugi_accum, dim3((nb * nb + 255) / 256), dim3(256), 0, s, Cm, nb, transpose, coef, accum);
+      CNPC_HIP(hipGetLastError());
+      return CNPC_OK;
+    }
     hipLaunchKernelGGL((k_sugi_w<T>), dim3(gw), dim3(256), 0, s, n3, nb, X, Z1, c1, Y, Z2, c2, slotW);
     CNPC_HIP(hipGetLastError());
     ContractCols cc;
@@ -444,8 +452,6 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
       } else {
         CNPC_TRY(contract_mfma_fp<T>(fields, n3, 2 * nb + 1, nb + 1, cc, partial, Cm, s, P->d_pairs, nb));
       }
-    } else {
-      CNPC_TRY(contract_mfma_fp<T>(fields, n3, 2 * nb + 1, nb + 1, cc, partial, Cm, s, P->d_pairs, nb));
     }
     hipLaunchKernelGGL(k_sugi_accum, dim3((nb * nb + 255) / 256), dim3(256), 0, s, Cm, nb, transpose, coef, accum);
     CNPC_HIP(hipGetLastError());
@@ -454,6 +460,12 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
   // sum_x P_i P_j g over the pairs i <= j of the nb fields of P, with g copied
   // into the all-ones slot for the call (one column; restored afterwards)
   auto contract_self = [&](double coef) -> cnpc_status {
+    if constexpr (sizeof(T) == 8) {
+      CNPC_TRY(contract_cross_sym(slotP, slotG, nb, n3, partial, Cm, s));
+      hipLaunchKernelGGL(k_sugi_accum, dim3((nb * nb + 255) / 256), dim3(256), 0, s, Cm, nb, 2, coef, accum);
+      CNPC_HIP(hipGetLastError());
+      return CNPC_OK;
+    }
     CNPC_HIP(hipMemcpyAsync(slotOne, slotG, sizeof(T) * (size_t)n3, hipMemcpyDeviceToDevice, s));
     ContractCols cc;
     cc.ncols = 1;
@@ -464,8 +476,6 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
       } else {
         CNPC_TRY(contract_mfma_fp<T>(fields, n3, nb + 1, nb, cc, partial, Cm, s));
       }
-    } else {
-      CNPC_TRY(contract_mfma_fp<T>(fields, n3, nb + 1, nb, cc, partial, Cm, s));
     }
     hipLaunchKernelGGL(k_sugi_accum, dim3((nb * nb + 255) / 256), dim3(256), 0, s, Cm, nb, 2, coef, accum);
     CNPC_HIP(hipGetLastError());
