@@ -538,25 +538,24 @@ cnpc_status cnpc_ktimer_stop(double* ms_per_class, int64_t* launches_per_class);
  *   CNPC_TUNE_CONTRACT_KG  point groups per contraction workgroup (1, 2, 4).
  *   CNPC_TUNE_SORT_PER     particles per thread of the sort scatter (1, 2, 4).
  *   CNPC_TUNE_SORT_THREADS threads per sort-scatter workgroup (512, 1024).
- *   CNPC_TUNE_SORT_FUSED   cnpc_paint_fkp on meshes of more than one tile
- *                          bucket: 0 (default) takes the catalog sums, the
- *                          tile histogram and the first sort step in one read
- *                          of each catalog; 1 takes the sums and histogram in
- *                          a read of their own; 2 keeps the histogram and the
- *                          l = 0 sums in the first sort step and takes the
- *                          Y_lm sums (l = 2, 4) in a read of their own
- *                          (identical meshes up to the rounding of alpha,
- *                          sums equal to a few ulp).
+ *   CNPC_TUNE_SORT_FUSED   painting on meshes of more than one tile bucket:
+ *                          0 (default) takes the l = 0 catalog sums, the tile
+ *                          histogram and the first sort step in one read of
+ *                          each catalog and the Y_lm sums (l = 2, 4), when
+ *                          wanted, in a read of their own; 1 takes all sums and
+ *                          the histogram in a read of their own; 2 as 0
+ *                          (identical meshes up to the rounding of alpha, sums
+ *                          equal to a few ulp).
  *   CNPC_TUNE_FOLD_FUSED   cnpc_paint_deinterlace and the batch runner: 0
  *                          (default) sums the tile blocks inside the z passes
  *                          of the de-interlacing transforms; 1 writes the
  *                          delta and N meshes and transforms them.
  *   CNPC_TUNE_BUCKET       shape of the first sort step of unweighted catalogs
  *                          (0: 1024 threads x 8 particles on one workgroup per
- *                          CU with the l = 0 sums, x 4 with Y_lm sums; 1: 1024
- *                          x 2 with the next chunk loaded during the current
- *                          one; 2: 512 x 4, likewise; 3: 1024 x 4 on two
- *                          workgroups per CU).
+ *                          CU, x 4 or 2 for catalogs too small to fill the CUs;
+ *                          1: 1024 x 2 with the next chunk loaded during the
+ *                          current one; 2: 512 x 4, likewise; 3: 1024 x 4 on
+ *                          two workgroups per CU).
  *   CNPC_TUNE_YLM_BASIS    Y_lm z passes of N = 64 .. 512 with register passes
  *                          (FP32 of 64, 256: bands kz < 4 sqrt(N)): 0
  *                          (default) transforms

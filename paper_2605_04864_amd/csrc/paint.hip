@@ -95,10 +95,34 @@ struct CountArgs {
 };
 
 // ------------------------------------------------------------ catalog sums --
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;
+// v shifted by one DPP control word (zero where it takes from no lane)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t b = __double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, ROWS, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
 }
+
+// sum over the wavefront, in every lane.  Row shifts and row broadcasts on the
+// VALU: as 64-bit lane permutes through the LDS pipe, the 21 sums of a
+// 1024-thread workgroup took 13 us at the end of every sums and bucket pass.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_f64<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8: lane 15 of each row of 16 holds the row's sum
+  v += dpp_f64<0x112, 0xf>(v);
+  v += dpp_f64<0x114, 0xf>(v);
+  v += dpp_f64<0x118, 0xf>(v);
+  v += dpp_f64<0x142, 0xa>(v);  // row_bcast:15 into rows 1, 3
+  v += dpp_f64<0x143, 0xc>(v);  // row_bcast:31 into rows 2, 3
+  const uint64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, 63);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 63);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+
+// columns of the catalog sums that LMAX leaves non-zero (the imaginary part of
+// every m = 0 sum is zero too)
+__host__ __device__ constexpr int sums_used(int lmax) { return lmax >= 4 ? CNPC_SUMS_LEN : lmax >= 2 ? 11 : 4; }
 
 constexpr int SUMS_THREADS = 1024;
 constexpr int SUMS_BLOCKS = 256;
@@ -207,7 +231,7 @@ __global__ void __launch_bounds__(SUMS_THREADS) k_catalog_sums(const uint32_t* _
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
   for (int q = 0; q < CNPC_SUMS_LEN; ++q) {
-    const double v = wave_sum(acc[q]);
+    const double v = q < sums_used(LMAX) ? wave_sum(acc[q]) : 0.0;
     if (lane == 0) red[wv][q] = v;
   }
   __syncthreads();
@@ -519,8 +543,11 @@ __global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ p
 }
 
 // ------------------------------------------------------ fused bucket pass --
-// One read of a catalog does the FP64 catalog sums, the tile histogram and the
-// first counting-sort step.  Buckets have a fixed capacity `cap` (bucket b at
+// One read of a catalog does the FP64 l = 0 catalog sums, the tile histogram and
+// the first counting-sort step.  (Y_lm sums take a read of their own: formed
+// here, between the barriers of the sort, their FP64 arithmetic cost more than
+// that read, 476 against 199 + 140 us for 3.0e7 particles, 4.9 against
+// 2.5 + 1.3 ms for 3.3e8.)  Buckets have a fixed capacity `cap` (bucket b at
 // region + b cap): a workgroup reserves its run in bucket b with one atomic on
 // bcnt[b] and sends whatever would pass the capacity to the overflow region
 // (reserved on *ovf), which the tile pass takes as chunks of mixed buckets.
@@ -551,7 +578,7 @@ __host__ __device__ constexpr size_t bucket_pass_lds(int per, int rs, int nbucke
 }
 
 // PF: the next chunk's particles are loaded while the current one is sorted
-template <int RS, int PER, int NT, int LMAX, bool PF>
+template <int RS, int PER, int NT, bool PF>
 __global__ void __launch_bounds__(NT) k_bucket_pass(const uint32_t* __restrict__ pos, const float* __restrict__ w,
                                                     int64_t n, SumsArgs sa, BucketArgs ba,
                                                     Rec<RS>* __restrict__ region, Rec<RS>* __restrict__ ovf_out) {
@@ -619,7 +646,7 @@ __global__ void __launch_bounds__(NT) k_bucket_pass(const uint32_t* __restrict__
         if (lds_tiles) atomicAdd(&ltile[t], 1u);
         rank[k] = atomicAdd(&hist[key[k]], 1u);
         const double wi = RS == 4 ? (double)__uint_as_float(r[k].v[3]) : 1.0;
-        sums_add<LMAX>(acc, r[k].v[0], r[k].v[1], r[k].v[2], wi, scale, sa);
+        sums_add<0>(acc, r[k].v[0], r[k].v[1], r[k].v[2], wi, scale, sa);
       }
     }
     __syncthreads();
@@ -677,7 +704,7 @@ __global__ void __launch_bounds__(NT) k_bucket_pass(const uint32_t* __restrict__
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
   for (int q = 0; q < CNPC_SUMS_LEN; ++q) {
-    const double v = wave_sum(acc[q]);
+    const double v = q < sums_used(0) ? wave_sum(acc[q]) : 0.0;
     if (lane == 0) red[wv * CNPC_SUMS_LEN + q] = v;
   }
   __syncthreads();
@@ -1422,7 +1449,7 @@ static TileGeom tile_geom(const cnpc_mesh_desc* d);
 
 static cnpc_status sums_counted(const cnpc_mesh_desc* d, const uint32_t* pos, const float* w, int64_t n,
                                 int lmax, double* sums, double* partial, const CountArgs& ca, hipStream_t s) {
-  const int nblocks = SUMS_BLOCKS;
+  const int nblocks = (int)std::max<int64_t>(1, std::min<int64_t>(SUMS_BLOCKS, (n + SUMS_THREADS - 1) / SUMS_THREADS));
   SumsArgs a;
   a.lmax = lmax;
   a.boxsize = d->boxsize;
@@ -1669,65 +1696,43 @@ static cnpc_status sort_and_paint(const cnpc_mesh_desc* d, const uint32_t* pos, 
 // catalog (fused bucket pass), then the tile painting.  sums: CNPC_SUMS_LEN
 // doubles (device).
 // Bucket-pass shape: CNPC_TUNE_BUCKET 0 (default) 1024 threads; unweighted
-// catalogs with the l = 0 sums 8 particles per thread on at most 256
-// workgroups (one per CU: 130 KB of LDS), with Y_lm sums 4 on at most 512;
-// fewer per thread where such chunks would fill less than 96 CUs (4 up to
-// 7.9e5 particles, 2 up to 2.0e5);
-// weighted catalogs 2 on at most 512.  1: 1024 threads, 2 particles, next
-// chunk prefetched; 2: 512 threads, 4 particles, prefetched; 3: 1024 threads,
-// 4 particles on at most 512 workgroups.  The prefetching forms exist for
-// unweighted catalogs with l = 0 or l <= 4 sums; the rest take 0.
+// catalogs 8 particles per thread on at most 256 workgroups (one per CU: 130 KB
+// of LDS), fewer per thread where such chunks would fill less than 96 CUs (4 up
+// to 7.9e5 particles, 2 up to 2.0e5); weighted catalogs 2 on at most 512.  1:
+// 1024 threads, 2 particles, next chunk prefetched; 2: 512 threads, 4
+// particles, prefetched; 3: 1024 threads, 4 particles on at most 512
+// workgroups (1 to 3: unweighted catalogs).
 struct BucketShape {
   int nt, per;
   bool pf;
   int maxblk;  // persistent workgroups at most
 };
-static BucketShape bucket_shape(int rs, int lmax, int64_t n) {
+static BucketShape bucket_shape(int rs, int64_t n) {
   const int v = tune_value(CNPC_TUNE_BUCKET);
-  if (rs == 3 && (lmax == 0 || lmax >= 4)) {
+  if (rs == 3) {
     if (v == 1) return {1024, 2, true, BUCKET_BLOCKS_MAX};
     if (v == 2) return {512, 4, true, BUCKET_BLOCKS_MAX};
   }
-  if (rs == 4) return {BUCKET_NT, 2, false, BUCKET_BLOCKS_MAX};
-  if (n <= (int64_t)BUCKET_NT * 2 * 96) return {BUCKET_NT, 2, false, BUCKET_BLOCKS_MAX};
-  if (v == 3 || lmax > 0 || n <= (int64_t)BUCKET_NT * 8 * 96) return {BUCKET_NT, 4, false, BUCKET_BLOCKS_MAX};
+  if (rs == 4 || n <= (int64_t)BUCKET_NT * 2 * 96) return {BUCKET_NT, 2, false, BUCKET_BLOCKS_MAX};
+  if (v == 3 || n <= (int64_t)BUCKET_NT * 8 * 96) return {BUCKET_NT, 4, false, BUCKET_BLOCKS_MAX};
   return {BUCKET_NT, 8, false, BUCKET_BLOCKS_MAX / 2};
 }
 
-template <int RS, int LMAX>
+template <int RS>
 static void launch_bucket_pass(const BucketShape& b, unsigned nblk, size_t lds, const uint32_t* pos, const float* w,
                                int64_t n, const SumsArgs& sa, const BucketArgs& ba, Rec<RS>* region,
                                Rec<RS>* ovf_out, hipStream_t s) {
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nblk), dim3(b.nt), lds, s, pos, w, n, sa, ba, region, ovf_out);
+  };
   if constexpr (RS == 3) {
-    if constexpr (LMAX != 2) {
-      if (b.pf && b.nt == 1024) {
-        hipLaunchKernelGGL((k_bucket_pass<3, 2, 1024, LMAX, true>), dim3(nblk), dim3(1024), lds, s, pos, w, n, sa,
-                           ba, region, ovf_out);
-        return;
-      }
-      if (b.pf) {
-        hipLaunchKernelGGL((k_bucket_pass<3, 4, 512, LMAX, true>), dim3(nblk), dim3(512), lds, s, pos, w, n, sa, ba,
-                           region, ovf_out);
-        return;
-      }
-    }
-    if constexpr (LMAX == 0) {
-      if (b.per == 8) {
-        hipLaunchKernelGGL((k_bucket_pass<3, 8, BUCKET_NT, 0, false>), dim3(nblk), dim3(BUCKET_NT), lds, s, pos, w,
-                           n, sa, ba, region, ovf_out);
-        return;
-      }
-    }
-    if (b.per == 2) {
-      hipLaunchKernelGGL((k_bucket_pass<3, 2, BUCKET_NT, LMAX, false>), dim3(nblk), dim3(BUCKET_NT), lds, s, pos, w, n,
-                         sa, ba, region, ovf_out);
-      return;
-    }
-    hipLaunchKernelGGL((k_bucket_pass<3, 4, BUCKET_NT, LMAX, false>), dim3(nblk), dim3(BUCKET_NT), lds, s, pos, w, n,
-                       sa, ba, region, ovf_out);
+    if (b.pf && b.nt == 1024) go(k_bucket_pass<3, 2, 1024, true>);
+    else if (b.pf) go(k_bucket_pass<3, 4, 512, true>);
+    else if (b.per == 8) go(k_bucket_pass<3, 8, BUCKET_NT, false>);
+    else if (b.per == 2) go(k_bucket_pass<3, 2, BUCKET_NT, false>);
+    else go(k_bucket_pass<3, 4, BUCKET_NT, false>);
   } else {
-    hipLaunchKernelGGL((k_bucket_pass<4, 2, BUCKET_NT, LMAX, false>), dim3(nblk), dim3(BUCKET_NT), lds, s, pos, w, n,
-                       sa, ba, region, ovf_out);
+    go(k_bucket_pass<4, 2, BUCKET_NT, false>);
   }
 }
 
@@ -1746,12 +1751,8 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   Rec<RS>* ovf_rec = reinterpret_cast<Rec<RS>*>(ws + L.off_ovf);
   double* partial = reinterpret_cast<double*>(ws + L.off_partial);
   const uint32_t cap = bucket_cap(n, L.nbuckets);  // <= L.cap
-  // knob value 2 of CNPC_TUNE_SORT_FUSED: the Y_lm sums (l = 2, 4) in a pass
-  // of their own, which keeps the bucket pass at the register count of the
-  // l = 0 sums
-  const bool split_sums = sums_lmax >= 2 && tune_value(CNPC_TUNE_SORT_FUSED) == 2;
-  const int lm = split_sums ? 0 : (sums_lmax >= 4 ? 4 : (sums_lmax >= 2 ? 2 : 0));
-  BucketShape bs = bucket_shape(RS, lm, n);
+  const bool split_sums = sums_lmax >= 2;  // Y_lm sums in a read of their own
+  BucketShape bs = bucket_shape(RS, n);
   const int ltiles = L.ntiles <= LDS_TILES_MAX ? L.ntiles : 0;
   const bool pack = packs_records(sizeof(T) == 4, RS, g.shift);  // records of the FP32 painter
   const bool packb = pack && L.ntiles <= 65536;                  // bucket records packed too
@@ -1790,9 +1791,7 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   ba.rkey = reinterpret_cast<uint16_t*>(reinterpret_cast<uint64_t*>(region) + (int64_t)L.nbuckets * cap);
   ba.okey = reinterpret_cast<uint16_t*>(reinterpret_cast<uint64_t*>(ovf_rec) + n);
   kt_begin(CNPC_KT_SORT, s);
-  if (lm == 4) launch_bucket_pass<RS, 4>(bs, nblk, lds, pos, w, n, sa, ba, region, ovf_rec, s);
-  else if (lm == 2) launch_bucket_pass<RS, 2>(bs, nblk, lds, pos, w, n, sa, ba, region, ovf_rec, s);
-  else launch_bucket_pass<RS, 0>(bs, nblk, lds, pos, w, n, sa, ba, region, ovf_rec, s);
+  launch_bucket_pass<RS>(bs, nblk, lds, pos, w, n, sa, ba, region, ovf_rec, s);
   kt_end(CNPC_KT_SORT, s);
   CNPC_HIP(hipGetLastError());
   const int per_bucket = 1 << (3 * g.ls);

@@ -231,8 +231,7 @@ def measure_pk(desc, gpos, rpos, bins, ells=(0, 2, 4), modified=False, gw=None, 
     """Yamamoto P_l (and P_ll', P_4b, P_6b, P_8b when modified) of one catalog pair.
     Odd l in ells (1, 3) give the imaginary-part multipoles, with no shot noise."""
     sc = scratch or Scratch()
-    norms, _, _ = catalog_norms(desc, gpos, rpos, gw, rw, sc, stream)
-    delta, _ = paint(desc, gpos, rpos, norms, gw, rw, noise=False, scratch=sc, stream=stream)
+    norms, delta, _, _, _ = paint_fkp(desc, gpos, rpos, gw, rw, noise=False, scratch=sc, stream=stream)
     kmax = bins.kmin + bins.nbins * bins.dk
     band = L.lib.cnpc_band_for(C.byref(desc), kmax)
     hi = [l for l in ells if l > 0]
@@ -283,8 +282,7 @@ def measure_pk_cross(desc, cat_a, cat_b, bins, ells=(0, 2, 4), scratch: Optional
         g, r = cat[0], cat[1]
         gw = cat[2] if len(cat) > 2 else None
         rw = cat[3] if len(cat) > 3 else None
-        nm, _, _ = catalog_norms(desc, g, r, gw, rw, sc, stream)
-        delta, _ = paint(desc, g, r, nm, gw, rw, noise=False, scratch=sc, stream=stream)
+        nm, delta, _, _, _ = paint_fkp(desc, g, r, gw, rw, noise=False, scratch=sc, stream=stream)
         hi = [l for l in want if l > 0]
         D, dint = deinterlace(desc, band, delta, want_real=len(hi) > 0, scratch=sc, stream=stream)
         del delta
@@ -378,8 +376,7 @@ def measure_bk(desc, gpos, rpos, bins, estimator=L.EST_SCOCCIMARRO, ell=0, preci
         precision = L.PREC_F64 if desc.dtype == L.F64 else L.PREC_F32
     plan = bispec_plan(desc, bins, estimator, ell, precision, sc, stream)
     band = plan.band
-    norms, _, _ = catalog_norms(desc, gpos, rpos, gw, rw, sc, stream)
-    delta, nmesh = paint(desc, gpos, rpos, norms, gw, rw, noise=shot_noise, scratch=sc, stream=stream)
+    norms, delta, nmesh, _, _ = paint_fkp(desc, gpos, rpos, gw, rw, noise=shot_noise, scratch=sc, stream=stream)
     D, dint = deinterlace(desc, band, delta, want_real=ell > 0, scratch=sc, stream=stream)
     del delta
     F0 = assemble(desc, band, 0, spec0=D, stream=stream)
@@ -461,8 +458,7 @@ def measure_sugiyama(desc, gpos, rpos, bins, l1, l2, L_, precision=None, gw=None
         precision = L.PREC_F64 if desc.dtype == L.F64 else L.PREC_F32
     plan = sugi_plan(desc, bins, l1, l2, L_, precision)
     band = plan.band
-    norms, _, _ = catalog_norms(desc, gpos, rpos, gw, rw, sc, stream)
-    delta, nmesh = paint(desc, gpos, rpos, norms, gw, rw, noise=shot_noise, scratch=sc, stream=stream)
+    norms, delta, nmesh, _, _ = paint_fkp(desc, gpos, rpos, gw, rw, noise=shot_noise, scratch=sc, stream=stream)
     D, dint = deinterlace(desc, band, delta, want_real=L_ > 0, scratch=sc, stream=stream)
     del delta
     F0 = assemble(desc, band, 0, spec0=D, stream=stream)
