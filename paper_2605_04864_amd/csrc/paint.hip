@@ -941,44 +941,28 @@ __global__ void __launch_bounds__(NT) k_tile_pass_packed(const uint64_t* __restr
 }
 
 // ------------------------------------------------------------------ paint --
-// 1-D stencil: node offsets relative to the base cell c = floor(u) and weights.
-template <typename T>
-__device__ __forceinline__ int stencil_1d(uint32_t p, int shift, int assign, int phase, T* wt) {
-  const uint32_t mask = (shift >= 32) ? 0xffffffffu : ((1u << shift) - 1u);
-  const int64_t f = (int64_t)(p & mask);
-  const int64_t one = (int64_t)1 << shift, half = one >> 1;
-  const T inv = T(1) / T(one);
-  if (assign == CNPC_TSC) {
-    // phase A: i = floor(u + 1/2); phase B: i = floor(u) (u - 1/2 + 1/2)
-    int off;
-    int64_t dfix;
-    if (phase == 0) {
-      if (f >= half) { off = 1; dfix = f - one; } else { off = 0; dfix = f; }
-    } else {
-      off = 0;
-      dfix = f - half;
-    }
-    const T d = T(dfix) * inv;
+// 1-D stencil: weights and the offset of the first node relative to the base
+// cell c = floor(u), from the fraction bits (shift <= 28).  TSC phase A:
+// i = floor(u + 1/2); phase B: i = floor(u) (u - 1/2 + 1/2).  CIC phase A: nodes
+// c, c + 1; phase B: u - 1/2.
+template <typename T, int ASSIGN>
+__device__ __forceinline__ int stencil_1d(uint32_t p, int shift, int phase, T inv, T* wt) {
+  const int one = 1 << shift, half = one >> 1;
+  const int f = (int)(p & (uint32_t)(one - 1));
+  const bool up = f >= half;
+  if constexpr (ASSIGN == CNPC_TSC) {
+    const T d = T(phase == 0 ? (up ? f - one : f) : f - half) * inv;
     const T a = T(0.5) - d, b = T(0.5) + d;
     wt[0] = T(0.5) * a * a;
     wt[1] = T(0.75) - d * d;
     wt[2] = T(0.5) * b * b;
-    return off - 1;  // first node offset
-  }
-  // CIC: phase A: nodes c, c+1 with d = frac; phase B: u - 1/2
-  if (phase == 0) {
-    const T d = T(f) * inv;
+    return phase == 0 ? (up ? 0 : -1) : -1;
+  } else {
+    const T d = T(phase == 0 ? f : (up ? f - half : f + half)) * inv;
     wt[0] = T(1) - d;
     wt[1] = d;
-    return 0;
+    return phase == 0 ? 0 : (up ? 0 : -1);
   }
-  int off;
-  int64_t dfix;
-  if (f >= half) { off = 0; dfix = f - half; } else { off = -1; dfix = f + half; }
-  const T d = T(dfix) * inv;
-  wt[0] = T(1) - d;
-  wt[1] = d;
-  return off;
 }
 
 // Contributions are accumulated as 64-bit fixed point (2^-40 units) with
@@ -987,63 +971,92 @@ __device__ __forceinline__ int stencil_1d(uint32_t p, int shift, int assign, int
 // depend on the order in which the threads add (bit-reproducible blocks).
 constexpr double FIX_SCALE = 1099511627776.0;  // 2^40
 constexpr double FIX_INV = 1.0 / 1099511627776.0;
+// |x| < 2^51: round(x) as a 64-bit integer, from the mantissa of x + 1.5 2^52 (one
+// addition, rounding to nearest even, and one 32-bit subtraction; the
+// conversion to a 64-bit integer takes a dozen instructions)
+constexpr double FIX_MAGIC = 6755399441055744.0;
+__device__ __forceinline__ unsigned long long fix_bits(double x_plus_magic) {
+  const uint64_t b = (uint64_t)__double_as_longlong(x_plus_magic);
+  return ((uint64_t)((uint32_t)(b >> 32) - 0x43380000u) << 32) | (uint32_t)b;
+}
 
-template <typename T, int ASSIGN, int RS>
-__global__ void __launch_bounds__(1024) k_paint_tiles(const Rec<RS>* __restrict__ rec,
-                                                     const uint32_t* __restrict__ start,
-                                                     const uint32_t* __restrict__ count, TileGeom g,
-                                                     int nphase, int ph0, int nph, int power,
-                                                     T* __restrict__ blocks) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  unsigned long long* acc = reinterpret_cast<unsigned long long*>(smem_raw);  // [nph][BVOL]
-  const int t = blockIdx.x;  // tile (tx * nt + ty) * nt + tz
-  const int shift = g.shift;
-  for (int i = threadIdx.x; i < nph * BVOL; i += blockDim.x) acc[i] = 0ull;
-  __syncthreads();
-  const int key = key_of(t / (g.nt * g.nt), (t / g.nt) % g.nt, t % g.nt, g);
-  const uint32_t s0 = start[key], cnt = count[key];
+// adds one particle to the block; FAST: |weight| < 1024, so that every
+// contribution is below 2^51 units
+template <typename T, int ASSIGN, bool FAST>
+__device__ __forceinline__ void paint_one(unsigned long long* __restrict__ acc, T wv, const T* wx, const T* wy,
+                                          const T* wz, int a1, int a0) {
   constexpr int NP = ASSIGN == CNPC_TSC ? 3 : 2;
-  for (uint32_t k = threadIdx.x; k < cnt; k += blockDim.x) {
-    const Rec<RS> p = rec[(int64_t)s0 + k];
-    const uint32_t px = p.v[0], py = p.v[1], pz = p.v[2];
-    T wv = T(1);
-    if constexpr (RS == 4) {
-      wv = T(__uint_as_float(p.v[3]));
-      if (power == 2) wv *= wv;
-    }
-  const int bx = ((int)(px >> shift) & 15) + 1;
-    const int by = ((int)(py >> shift) & 15) + 1;
-    const int bz = ((int)(pz >> shift) & 15) + 1;
-    for (int q = 0; q < nph; ++q) {
-      const int ph = ph0 + q;
-      T wx[3], wy[3], wz[3];
-      const int ox = stencil_1d<T>(px, shift, ASSIGN, ph, wx);
-      const int oy = stencil_1d<T>(py, shift, ASSIGN, ph, wy);
-      const int oz = stencil_1d<T>(pz, shift, ASSIGN, ph, wz);
-      // node lz = bz + oz + iz sits at lz - 1 in its row, lz = 0 at 18
-      const int a1 = q * BVOL + (bx + ox) * BW * BW + (by + oy) * BW + (bz + oz - 1);
-      const int a0 = a1 + (bz + oz == 0 ? BW : 0);
 #pragma unroll
-      for (int ix = 0; ix < NP; ++ix) {
-        const T vx = wv * wx[ix];
+  for (int ix = 0; ix < NP; ++ix) {
+    // FP64: the unit scale goes into the x weight (a power of two, exact)
+    const T vx = sizeof(T) == 8 && FAST ? wv * wx[ix] * T(FIX_SCALE) : wv * wx[ix];
 #pragma unroll
-        for (int iy = 0; iy < NP; ++iy) {
-          const T vxy = vx * wy[iy];
+    for (int iy = 0; iy < NP; ++iy) {
+      const T vxy = vx * wy[iy];
 #pragma unroll
-          for (int iz = 0; iz < NP; ++iz) {
-            const long long fixv = __double2ll_rn((double)(vxy * wz[iz]) * FIX_SCALE);
-            atomicAdd(&acc[(iz == 0 ? a0 : a1) + ix * BW * BW + iy * BW + iz], (unsigned long long)fixv);
-          }
-        }
+      for (int iz = 0; iz < NP; ++iz) {
+        unsigned long long fix;
+        if constexpr (!FAST) fix = (unsigned long long)__double2ll_rn((double)(vxy * wz[iz]) * FIX_SCALE);
+        else if constexpr (sizeof(T) == 8) fix = fix_bits(__builtin_fma((double)vxy, (double)wz[iz], FIX_MAGIC));
+        else fix = fix_bits(__builtin_fma((double)(vxy * wz[iz]), FIX_SCALE, FIX_MAGIC));
+        atomicAdd(&acc[(iz == 0 ? a0 : a1) + ix * BW * BW + iy * BW + iz], fix);
       }
     }
   }
-  __syncthreads();
-  T* out = blocks + ((int64_t)t * nphase + ph0) * BSTRIDE;
-  for (int i = threadIdx.x; i < nph * BVOL; i += blockDim.x) {
-    const int q = i >= BVOL ? 1 : 0;
-    out[q * BSTRIDE + i - q * BVOL] = T((double)(long long)acc[i] * FIX_INV);
+}
+
+// A workgroup paints one tile, interlacing phase and weight power (w into
+// blocks1, w^2 into blocks2; npow 1: w alone): its 55 KB block leaves room for
+// two workgroups per CU, 8 wavefronts per SIMD (both phases in one workgroup
+// left 4).  The workgroups of a tile are 8 apart in launch order, so that they
+// run on one XCD and read its records from that L2.  Bound by the 64-bit LDS
+// atomics (27 TSC or 8 CIC per particle, phase and power).  256^3 TSC
+// interlaced, 3.0e7 particles: FP64 843 us with conversion calls and one
+// workgroup per CU before, 638 us here; weighted FP32, 1.9e7 particles, both
+// powers: 1270 us before, 932 us here.
+template <typename T, int ASSIGN, int RS>
+__global__ void __launch_bounds__(1024, 8) k_paint_tiles(const Rec<RS>* __restrict__ rec,
+                                                     const uint32_t* __restrict__ start,
+                                                     const uint32_t* __restrict__ count, TileGeom g,
+                                                     int nphase, int npow, T* __restrict__ blocks1,
+                                                     T* __restrict__ blocks2) {
+  __shared__ __align__(16) unsigned long long acc[BVOL];
+  const int nsub = nphase * npow;
+  int t, sub;  // tile (tx * nt + ty) * nt + tz
+  if (g.nt > 1) {
+    t = (int)(blockIdx.x / (8u * nsub)) * 8 + (int)(blockIdx.x & 7u);
+    sub = (int)(blockIdx.x >> 3) % nsub;
+  } else {
+    t = 0;
+    sub = (int)blockIdx.x;
   }
+  const int ph = nphase == 2 ? sub & 1 : 0, pw = nphase == 2 ? sub >> 1 : sub;
+  const int shift = g.shift;
+  for (int i = threadIdx.x; i < BVOL; i += 1024) acc[i] = 0ull;
+  __syncthreads();
+  const int key = key_of(t / (g.nt * g.nt), (t / g.nt) % g.nt, t % g.nt, g);
+  const uint32_t s0 = start[key], cnt = count[key];
+  const T inv = T(1) / T(1 << shift);
+  for (uint32_t k = threadIdx.x; k < cnt; k += 1024u) {
+    const Rec<RS> p = rec[(int64_t)s0 + k];
+    T wv = T(1);
+    if constexpr (RS == 4) {
+      wv = T(__uint_as_float(p.v[3]));
+      if (pw == 1) wv *= wv;
+    }
+    T wx[3], wy[3], wz[3];
+    const int lx = ((int)(p.v[0] >> shift) & 15) + 1 + stencil_1d<T, ASSIGN>(p.v[0], shift, ph, inv, wx);
+    const int ly = ((int)(p.v[1] >> shift) & 15) + 1 + stencil_1d<T, ASSIGN>(p.v[1], shift, ph, inv, wy);
+    const int lz = ((int)(p.v[2] >> shift) & 15) + 1 + stencil_1d<T, ASSIGN>(p.v[2], shift, ph, inv, wz);
+    // node lz + iz sits at lz + iz - 1 in its row, node 0 at 18
+    const int a1 = lx * BW * BW + ly * BW + lz - 1;
+    const int a0 = a1 + (lz == 0 ? BW : 0);
+    if (RS == 3 || fabs(wv) < T(1024)) paint_one<T, ASSIGN, true>(acc, wv, wx, wy, wz, a1, a0);
+    else paint_one<T, ASSIGN, false>(acc, wv, wx, wy, wz, a1, a0);
+  }
+  __syncthreads();
+  T* out = (pw ? blocks2 : blocks1) + ((int64_t)t * nphase + ph) * BSTRIDE;
+  for (int i = threadIdx.x; i < BVOL; i += 1024) out[i] = T((double)(long long)acc[i] * FIX_INV);
 }
 
 // Unit-weight FP32 painting with 32-bit LDS atomics.  Each round of the
@@ -1623,36 +1636,25 @@ static cnpc_status paint_sorted(const cnpc_mesh_desc* d, bool weighted, int set0
   uint32_t* count = reinterpret_cast<uint32_t*>(ws + L.off_count[set0]);
   uint32_t* start = reinterpret_cast<uint32_t*>(ws + L.off_start);
   Rec<RS>* rec = reinterpret_cast<Rec<RS>*>(ws + L.off_rec);
-  // phases per launch so that the 64-bit LDS blocks fit the workgroup limit
-  const int nph = ((size_t)L.nphase * BVOL * 8 <= lds_limit()) ? L.nphase : 1;
-  const size_t lds_paint = (size_t)nph * BVOL * 8;
-  const int npow = weighted ? 2 : 1;
-  for (int pw = 0; pw < npow; ++pw) {
-    T* blocks = reinterpret_cast<T*>(ws + L.off_blocks[set0 + 2 * pw]);
-    if constexpr (sizeof(T) == 4 && RS == 3) {
-      kt_begin(CNPC_KT_PAINT, s);
-      if (d->assign == CNPC_TSC)
-        hipLaunchKernelGGL((k_paint_tiles_u32<CNPC_TSC>), dim3(L.ntiles), dim3(PAINT32_THREADS), 0, s, rec, start,
-                           count, g, L.nphase, packs_records(true, 3, g.shift), reinterpret_cast<float*>(blocks));
-      else
-        hipLaunchKernelGGL((k_paint_tiles_u32<CNPC_CIC>), dim3(L.ntiles), dim3(PAINT32_THREADS), 0, s, rec, start,
-                           count, g, L.nphase, packs_records(true, 3, g.shift), reinterpret_cast<float*>(blocks));
-      kt_end(CNPC_KT_PAINT, s);
-      CNPC_HIP(hipGetLastError());
-      continue;
+  kt_begin(CNPC_KT_PAINT, s);
+  if constexpr (sizeof(T) == 4 && RS == 3) {
+    // unit weights: w^2 = w, the second power's blocks are painted alike
+    for (int pw = 0; pw < (weighted ? 2 : 1); ++pw) {
+      T* blocks = reinterpret_cast<T*>(ws + L.off_blocks[set0 + 2 * pw]);
+      hipLaunchKernelGGL((d->assign == CNPC_TSC ? k_paint_tiles_u32<CNPC_TSC> : k_paint_tiles_u32<CNPC_CIC>),
+                         dim3(L.ntiles), dim3(PAINT32_THREADS), 0, s, rec, start, count, g, L.nphase,
+                         packs_records(true, 3, g.shift), blocks);
     }
-    for (int ph0 = 0; ph0 < L.nphase; ph0 += nph) {
-      kt_begin(CNPC_KT_PAINT, s);
-      if (d->assign == CNPC_TSC)
-        hipLaunchKernelGGL((k_paint_tiles<T, CNPC_TSC, RS>), dim3(L.ntiles), dim3(1024), lds_paint, s, rec, start,
-                           count, g, L.nphase, ph0, nph, pw + 1, blocks);
-      else
-        hipLaunchKernelGGL((k_paint_tiles<T, CNPC_CIC, RS>), dim3(L.ntiles), dim3(1024), lds_paint, s, rec, start,
-                           count, g, L.nphase, ph0, nph, pw + 1, blocks);
-      kt_end(CNPC_KT_PAINT, s);
-      CNPC_HIP(hipGetLastError());
-    }
+  } else {
+    const int npow = weighted ? 2 : 1;
+    T* b1 = reinterpret_cast<T*>(ws + L.off_blocks[set0]);
+    T* b2 = weighted ? reinterpret_cast<T*>(ws + L.off_blocks[set0 + 2]) : nullptr;
+    hipLaunchKernelGGL((d->assign == CNPC_TSC ? k_paint_tiles<T, CNPC_TSC, RS> : k_paint_tiles<T, CNPC_CIC, RS>),
+                       dim3((unsigned)(L.ntiles * L.nphase * npow)), dim3(1024), 0, s, rec, start, count, g, L.nphase,
+                       npow, b1, b2);
   }
+  kt_end(CNPC_KT_PAINT, s);
+  CNPC_HIP(hipGetLastError());
   return CNPC_OK;
 }
 

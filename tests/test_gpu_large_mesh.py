@@ -117,3 +117,27 @@ def test_ylm_512_matches_field_transforms(dtype, tol):
             L.check(L.lib.cnpc_tune_set(L.TUNE["ylm_basis"][0], 0))
     for a, b in zip(out[0], out[1]):
         assert float((a - b).abs().max()) <= tol * float(b.abs().max())
+
+
+@pytest.mark.parametrize("dtype,tol", [(L.F32, 1e-6), (L.F64, 1e-12)])
+@pytest.mark.parametrize("n,assign", [(16, L.TSC), (16, L.CIC), (64, L.TSC), (64, L.CIC)])
+def test_paint_weights_beyond_the_mantissa_range(n, assign, dtype, tol):
+    """Weights of both signs below and above 1024 (w^2 up to 4e6): contributions
+    past 2^51 units take the 64-bit conversion, the others the mantissa."""
+    from oracle import mesh as oms
+    rng = np.random.default_rng(3)
+    cat = []
+    for k, m in enumerate((1501, 4099)):
+        w = np.where(rng.uniform(size=m) < 0.5, rng.uniform(0.5, 2.0, m), rng.uniform(900.0, 2000.0, m))
+        w = (w * np.where(rng.uniform(size=m) < 0.2, -1.0, 1.0)).astype(np.float32)
+        cat += [rng.integers(0, 1 << 32, (3, m), dtype=np.uint64).astype(np.uint32), w]
+    g, gw, r, rw = cat
+    d = cn.mesh_desc(n, 300.0, assign=assign, interlace=True, dtype=dtype)
+    dev = [torch.from_numpy(x).cuda() for x in cat]
+    norms, delta, noise, _, _ = pl.paint_fkp(d, dev[0], dev[2], dev[1], dev[3])
+    alpha = float(norms[L.NORM_ALPHA])
+    od, on = oms.paint_fkp(g, gw, r, rw, alpha, n, assign, True)
+    for got, ref in ((delta, od), (noise, on)):
+        for ph in range(2):
+            e = np.abs(got[ph].double().cpu().numpy() - ref[ph])
+            assert np.max(e) <= tol * np.max(np.abs(ref[ph]))
