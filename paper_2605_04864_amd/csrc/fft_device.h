@@ -278,6 +278,51 @@ __device__ __forceinline__ void row_fft_g(cx<T>* v, int t, cx<T>* buf, const cx<
   wave_lds_sync();  // the buffer may be written again
 }
 
+// Column analogue of row_fft_g: W columns side by side (128 bytes of a row),
+// lane (c, t) of N / 8 x W holds rows t + L r of column c on entry and exit;
+// buf: N W elements, row e of column c at group_row(e) W + c (rows of 128 bytes
+// alternate between the two halves of the banks; the swap by bit 3 keeps the
+// lanes of a store, 8 rows apart, in both).  tw: W_N^t at tw[TS t], conjugated
+// for CONJ.  The lanes of a column span the workgroup: four workgroup barriers,
+// the last after its last read of buf.
+__device__ __forceinline__ int group_row(int e) { return e ^ ((e >> 3) & 1); }
+
+template <typename T, int N, int W, int DIR, int TS = 1, bool CONJ = false>
+__device__ __forceinline__ void col_fft_g(cx<T>* v, int c, int t, cx<T>* buf, const cx<T>* tw) {
+  constexpr int L = N / 8, Q = N / 64;
+  static_assert(N == 128 || N == 256 || N == 512, "column groups: 128, 256, 512");
+  auto twid = [&](int i) { return CONJ ? cconj(tw[TS * i]) : tw[TS * i]; };
+  dft8<T, DIR>(v);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) buf[group_row(8 * t + r) * W + c] = v[r];
+  __syncthreads();
+  const int k = t & 7;
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const cx<T> a = buf[group_row(t + r * L) * W + c];
+    v[r] = r == 0 ? a : cmul(a, twid(r * k * (N / 64)));
+  }
+  __syncthreads();
+  dft8<T, DIR>(v);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) buf[group_row((t - k) * 8 + k + 8 * r) * W + c] = v[r];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 8 / Q; ++q) {
+    cx<T> u[Q];
+#pragma unroll
+    for (int r = 0; r < Q; ++r) {
+      const int j = t + L * q;
+      const cx<T> a = buf[group_row(j + 64 * r) * W + c];
+      u[r] = r == 0 ? a : cmul(a, twid(r * j));
+    }
+    dft_reg<T, Q, DIR>(u);
+#pragma unroll
+    for (int r = 0; r < Q; ++r) v[q + (8 / Q) * r] = u[r];
+  }
+  __syncthreads();
+}
+
 // Z[N - k] for k = t + L i of a sequence that row_fft_g left in v (lane L - t,
 // register 7 - i; lane 0 holds its own partners)
 template <typename T, int N>

@@ -141,3 +141,23 @@ def test_paint_weights_beyond_the_mantissa_range(n, assign, dtype, tol):
         for ph in range(2):
             e = np.abs(got[ph].double().cpu().numpy() - ref[ph])
             assert np.max(e) <= tol * np.max(np.abs(ref[ph]))
+
+
+@pytest.mark.parametrize("n,band,dtype", [(128, 64, L.F32), (128, 16, L.F64), (512, 64, L.F32), (512, 128, L.F64)])
+def test_deinterlace_fused_x_pass(n, band, dtype):
+    """The fused x pass of 128 and 512 (both phases forward, combination, band
+    copy, inverse) against the plain passes (CNPC_TUNE_FFT_PASSES 1)."""
+    d = cn.mesh_desc(n, 1000.0, interlace=True, dtype=dtype)
+    x = torch.randn((2, n, n, n), dtype=torch.float64, device="cuda",
+                    generator=torch.Generator(device="cuda").manual_seed(n)).to(pl._TORCH_DT[dtype])
+    out = {}
+    for knob in (0, 1):
+        L.check(L.lib.cnpc_tune_set(L.TUNE["fft_passes"][0], knob))
+        try:
+            out[knob] = pl.deinterlace(d, band, x)
+            torch.cuda.synchronize()
+        finally:
+            L.check(L.lib.cnpc_tune_set(L.TUNE["fft_passes"][0], 0))
+    tol = 1e-12 if dtype == L.F64 else 2e-6
+    for a, b in zip(out[0], out[1]):
+        assert float((a - b).abs().max()) <= tol * float(b.abs().max())
