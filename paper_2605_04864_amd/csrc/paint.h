@@ -24,7 +24,7 @@ struct PaintLayout {
   size_t off_rec, off_tmp;  // sorted records, bucket-ordered records (shared by both catalogs)
   size_t off_count[2];           // tile counts of the galaxy / random catalog
   size_t off_partial, off_sums;  // catalog-sum partials and sums (fused entry point)
-  size_t off_start, off_cursor, off_bcur;
+  size_t off_start, off_cursor, off_bcur, off_hist;
   size_t off_blocks[4];
   // fused bucket pass (entry point with catalog sums, more than one bucket):
   // fixed-capacity bucket regions, the overflow records, the bucket

@@ -180,14 +180,17 @@ __device__ __forceinline__ void sums_add(double* acc, uint32_t px, uint32_t py, 
   }
 }
 
-// LMAX: Y_lm sums for l <= LMAX (0, 2 or 4); the others stay zero
+// Catalog sums of one workgroup, block `blk` of `nblk` (LMAX: Y_lm sums for
+// l <= LMAX, 0, 2 or 4; the others stay zero) into partial[blk], and the tile
+// histogram of its particles: with `hist` stored there (at most 64 tiles), else
+// added to ca.count.
+constexpr int SMALL_TILES = 64;  // tiles of a mesh of one bucket, at most
 template <int LMAX>
-__global__ void __launch_bounds__(SUMS_THREADS) k_catalog_sums(const uint32_t* __restrict__ pos,
-                                                      const float* __restrict__ w, int64_t n,
-                                                      SumsArgs a, double* __restrict__ partial,
-                                                      CountArgs ca) {
+__device__ __forceinline__ void catalog_sums_block(const uint32_t* __restrict__ pos, const float* __restrict__ w,
+                                                   int64_t n, const SumsArgs& a, double* __restrict__ partial,
+                                                   const CountArgs& ca, uint32_t* __restrict__ hist, int blk, int nblk) {
   extern __shared__ uint32_t lcount[];
-  const bool count = ca.count != nullptr;
+  const bool count = ca.count != nullptr || hist != nullptr;
   const bool lds = count && ca.ntiles <= LDS_TILES_MAX;
   if (lds) {
     for (int t = threadIdx.x; t < ca.ntiles; t += blockDim.x) lcount[t] = 0;
@@ -200,8 +203,8 @@ __global__ void __launch_bounds__(SUMS_THREADS) k_catalog_sums(const uint32_t* _
   // U particles per thread and trip: all their loads are issued before any of
   // them is used (fewer for the larger register sets of l > 0)
   constexpr int U = LMAX == 0 ? 4 : (LMAX == 2 ? 2 : 1);
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i0 < n; i0 += U * stride) {
+  const int64_t stride = (int64_t)nblk * blockDim.x;
+  for (int64_t i0 = blk * (int64_t)blockDim.x + threadIdx.x; i0 < n; i0 += U * stride) {
     uint32_t px[U], py[U], pz[U];
     float wv[U];
 #pragma unroll
@@ -238,14 +241,51 @@ __global__ void __launch_bounds__(SUMS_THREADS) k_catalog_sums(const uint32_t* _
   if (threadIdx.x < CNPC_SUMS_LEN) {
     double v = 0.0;
     for (int k = 0; k < (int)(blockDim.x >> 6); ++k) v += red[k][threadIdx.x];
-    partial[(int64_t)blockIdx.x * CNPC_SUMS_LEN + threadIdx.x] = v;
+    partial[(int64_t)blk * CNPC_SUMS_LEN + threadIdx.x] = v;
   }
   if (lds) {
     for (int t = threadIdx.x; t < ca.ntiles; t += blockDim.x) {
       const uint32_t c = lcount[t];
-      if (c) atomicAdd(&ca.count[t], c);
+      if (hist) hist[(int64_t)blk * SMALL_TILES + t] = c;
+      else if (c) atomicAdd(&ca.count[t], c);
     }
   }
+}
+
+template <int LMAX>
+__global__ void __launch_bounds__(SUMS_THREADS) k_catalog_sums(const uint32_t* __restrict__ pos,
+                                                      const float* __restrict__ w, int64_t n,
+                                                      SumsArgs a, double* __restrict__ partial,
+                                                      CountArgs ca) {
+  catalog_sums_block<LMAX>(pos, w, n, a, partial, ca, nullptr, blockIdx.x, gridDim.x);
+}
+
+// Both catalogs of a painting, for the kernels that take them in one launch on
+// meshes of one tile bucket (blockIdx.y: galaxies, randoms).
+struct SmallCat {
+  const uint32_t* pos;
+  const float* w;
+  int64_t n;
+  int nblk;           // workgroups of its sums
+  double* partial;    // [nblk][CNPC_SUMS_LEN]
+  uint32_t* hist;     // [nblk][SMALL_TILES] tile histograms
+  uint32_t *count, *start, *cursor;  // [ntiles]
+  void* rec;          // tile-sorted records
+  double* sums;
+};
+struct SmallPair {
+  SmallCat c[2];
+};
+
+template <int LMAX>
+__global__ void __launch_bounds__(SUMS_THREADS) k_catalog_sums2(SmallPair sp, SumsArgs a, TileGeom g, int ntiles) {
+  const SmallCat c = sp.c[blockIdx.y];
+  if ((int)blockIdx.x >= c.nblk) return;
+  CountArgs ca;
+  ca.g = g;
+  ca.ntiles = ntiles;
+  ca.count = nullptr;
+  catalog_sums_block<LMAX>(c.pos, c.w, c.n, a, c.partial, ca, c.hist, blockIdx.x, c.nblk);
 }
 
 __global__ void __launch_bounds__(64) k_reduce_partials(const double* __restrict__ partial, int nblocks,
@@ -258,9 +298,8 @@ __global__ void __launch_bounds__(64) k_reduce_partials(const double* __restrict
   if (threadIdx.x == 0) out[q] = v;
 }
 
-__global__ void k_norms(const double* __restrict__ gs, const double* __restrict__ rs, int64_t ngal,
-                        double boxsize, double* __restrict__ nm) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__device__ __forceinline__ void form_norms(const double* gs, const double* rs, int64_t ngal, double boxsize,
+                                           double* __restrict__ nm) {
   const double alpha = gs[0] / rs[0];
   const double nbar = (double)ngal / (boxsize * boxsize * boxsize);
   const double I22 = alpha * nbar * rs[1];
@@ -273,6 +312,57 @@ __global__ void k_norms(const double* __restrict__ gs, const double* __restrict_
   nm[CNPC_NORM_SBAR] = gs[2] - alpha * alpha * alpha * rs[2];
   const double a3 = alpha * alpha * alpha;
   for (int q = 0; q < 2 * CNPC_NYLM_SUMS; ++q) nm[CNPC_NORM_SBARLM + q] = gs[3 + q] - a3 * rs[3 + q];
+}
+
+__global__ void k_norms(const double* __restrict__ gs, const double* __restrict__ rs, int64_t ngal,
+                        double boxsize, double* __restrict__ nm) {
+  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  form_norms(gs, rs, ngal, boxsize, nm);
+}
+
+// The steps between the sums and the sort of a mesh of one tile bucket, one
+// launch: workgroups 0, 1 add the tile histograms of a catalog's sums workgroups
+// and scan them (count, start, cursor); workgroup 2 forms the catalog sums of both
+// (k_reduce_partials' order) and, with nm, the norms.
+__global__ void __launch_bounds__(1024) k_small_scan(SmallPair sp, int ntiles, int64_t ngal, double boxsize,
+                                                     double* __restrict__ nm) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  if (blockIdx.x < 2) {
+    const SmallCat c = sp.c[blockIdx.x];
+    __shared__ uint32_t part[16][SMALL_TILES];
+    uint32_t v = 0;
+    if (lane < ntiles)
+      for (int b = wv; b < c.nblk; b += 16) v += c.hist[(int64_t)b * SMALL_TILES + lane];
+    part[wv][lane] = v;
+    __syncthreads();
+    if (wv) return;
+    uint32_t cnt = 0;
+    for (int k = 0; k < 16; ++k) cnt += part[k][lane];
+    uint32_t run = cnt;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t u = __shfl_up(run, off, 64);
+      if (lane >= off) run += u;
+    }
+    if (lane < ntiles) {
+      c.count[lane] = cnt;
+      c.start[lane] = run - cnt;
+      c.cursor[lane] = run - cnt;
+    }
+    return;
+  }
+  __shared__ double sums[2][CNPC_SUMS_LEN];
+  for (int q = wv; q < 2 * CNPC_SUMS_LEN; q += 16) {
+    const int k = q >= CNPC_SUMS_LEN ? 1 : 0, col = q - k * CNPC_SUMS_LEN;
+    double v = 0.0;
+    for (int b = lane; b < sp.c[k].nblk; b += 64) v += sp.c[k].partial[(int64_t)b * CNPC_SUMS_LEN + col];
+    v = wave_sum(v);
+    if (lane == 0) {
+      sums[k][col] = v;
+      sp.c[k].sums[col] = v;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && nm) form_norms(sums[0], sums[1], ngal, boxsize, nm);
 }
 
 // ------------------------------------------------------------------- sort --
@@ -462,12 +552,10 @@ __host__ __device__ constexpr size_t partition_lds(int per, int rs, int rcap, in
 // rcap the chunk takes one global atomic per particle instead.
 // cursor[key] hands out output slots (initialised to the key's start).
 template <bool SOA, bool FINE, int RS, int PER, int NT>
-__global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ pos,
-                                                            const float* __restrict__ w,
-                                                            const Rec<RS>* __restrict__ rin,
-                                                            int64_t n, TileGeom g, int rcap,
-                                                            uint32_t* __restrict__ cursor,
-                                                            Rec<RS>* __restrict__ rout, bool pack) {
+__device__ __forceinline__ void partition_block(const uint32_t* __restrict__ pos, const float* __restrict__ w,
+                                                const Rec<RS>* __restrict__ rin, int64_t n, const TileGeom& g,
+                                                int rcap, uint32_t* __restrict__ cursor, Rec<RS>* __restrict__ rout,
+                                                bool pack) {
   constexpr int CH = NT * PER;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   Rec<RS>* stage = reinterpret_cast<Rec<RS>*>(smem_raw);                        // [CH]
@@ -540,6 +628,25 @@ __global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ p
     const int kk = skey[j];
     put_rec(rout, gbase[kk] + (j - lstart[kk]), stage[j], FINE && pack, g.shift);
   }
+}
+
+template <bool SOA, bool FINE, int RS, int PER, int NT>
+__global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ pos,
+                                                            const float* __restrict__ w,
+                                                            const Rec<RS>* __restrict__ rin,
+                                                            int64_t n, TileGeom g, int rcap,
+                                                            uint32_t* __restrict__ cursor,
+                                                            Rec<RS>* __restrict__ rout, bool pack) {
+  partition_block<SOA, FINE, RS, PER, NT>(pos, w, rin, n, g, rcap, cursor, rout, pack);
+}
+
+// the one sort step of a mesh of one tile bucket, both catalogs in one launch
+template <int RS, int PER>
+__global__ void __launch_bounds__(1024) k_partition2(SmallPair sp, TileGeom g, int ntiles) {
+  const SmallCat c = sp.c[blockIdx.y];
+  if ((int64_t)blockIdx.x * 1024 * PER >= c.n) return;
+  partition_block<true, true, RS, PER, 1024>(c.pos, c.w, nullptr, c.n, g, ntiles, c.cursor,
+                                             reinterpret_cast<Rec<RS>*>(c.rec), false);
 }
 
 // ------------------------------------------------------ fused bucket pass --
@@ -965,6 +1072,15 @@ __device__ __forceinline__ int stencil_1d(uint32_t p, int shift, int phase, T in
   }
 }
 
+// Tile-sorted catalogs of a painting launch (blockIdx.y; one, or the two of a
+// mesh of one tile bucket); blocks[c], blocks[c + 2]: the w and w^2 blocks.
+template <typename T, int RS>
+struct PaintCats {
+  const Rec<RS>* rec[2];
+  const uint32_t *start[2], *count[2];
+  T* blocks[4];
+};
+
 // Contributions are accumulated as 64-bit fixed point (2^-40 units) with
 // integer LDS atomics: on gfx950 integer LDS atomics run at full rate while
 // FP32 LDS atomics are an order of magnitude slower, and integer sums do not
@@ -1015,11 +1131,10 @@ __device__ __forceinline__ void paint_one(unsigned long long* __restrict__ acc, 
 // workgroup per CU before, 638 us here; weighted FP32, 1.9e7 particles, both
 // powers: 1270 us before, 932 us here.
 template <typename T, int ASSIGN, int RS>
-__global__ void __launch_bounds__(1024, 8) k_paint_tiles(const Rec<RS>* __restrict__ rec,
-                                                     const uint32_t* __restrict__ start,
-                                                     const uint32_t* __restrict__ count, TileGeom g,
-                                                     int nphase, int npow, T* __restrict__ blocks1,
-                                                     T* __restrict__ blocks2) {
+__global__ void __launch_bounds__(1024, 8) k_paint_tiles(PaintCats<T, RS> pc, TileGeom g, int nphase, int npow) {
+  const Rec<RS>* __restrict__ rec = pc.rec[blockIdx.y];
+  const uint32_t* __restrict__ start = pc.start[blockIdx.y];
+  const uint32_t* __restrict__ count = pc.count[blockIdx.y];
   __shared__ __align__(16) unsigned long long acc[BVOL];
   const int nsub = nphase * npow;
   int t, sub;  // tile (tx * nt + ty) * nt + tz
@@ -1055,7 +1170,7 @@ __global__ void __launch_bounds__(1024, 8) k_paint_tiles(const Rec<RS>* __restri
     else paint_one<T, ASSIGN, false>(acc, wv, wx, wy, wz, a1, a0);
   }
   __syncthreads();
-  T* out = (pw ? blocks2 : blocks1) + ((int64_t)t * nphase + ph) * BSTRIDE;
+  T* out = pc.blocks[blockIdx.y + 2 * pw] + ((int64_t)t * nphase + ph) * BSTRIDE;
   for (int i = threadIdx.x; i < BVOL; i += 1024) out[i] = T((double)(long long)acc[i] * FIX_INV);
 }
 
@@ -1114,11 +1229,12 @@ __device__ __forceinline__ int stencil32(uint32_t p, int shift, int phase, float
 }
 
 template <int ASSIGN>
-__global__ void __launch_bounds__(PAINT32_THREADS, 8) k_paint_tiles_u32(const Rec<3>* __restrict__ rec,
-                                                                     const uint32_t* __restrict__ start,
-                                                                     const uint32_t* __restrict__ count,
-                                                                     TileGeom g, int nphase, bool packed,
-                                                                     float* __restrict__ blocks) {
+__global__ void __launch_bounds__(PAINT32_THREADS, 8) k_paint_tiles_u32(PaintCats<float, 3> pc, TileGeom g, int nphase,
+                                                                     bool packed) {
+  const Rec<3>* __restrict__ rec = pc.rec[blockIdx.y];
+  const uint32_t* __restrict__ start = pc.start[blockIdx.y];
+  const uint32_t* __restrict__ count = pc.count[blockIdx.y];
+  float* __restrict__ blocks = pc.blocks[blockIdx.y];
   constexpr float SCALE = 2097152.0f;  // 2^21
   constexpr int ROUNDS_PER_FLUSH = ASSIGN == CNPC_TSC ? 4 : 1;
   constexpr int NP = ASSIGN == CNPC_TSC ? 3 : 2;
@@ -1460,9 +1576,14 @@ __global__ void __launch_bounds__(256) k_fold_zr2c(FoldArgs<T> fa, const double*
 // ------------------------------------------------------------------- host --
 static TileGeom tile_geom(const cnpc_mesh_desc* d);
 
+// workgroups of a sums pass over n particles
+static int sums_blocks(int64_t n) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(SUMS_BLOCKS, (n + SUMS_THREADS - 1) / SUMS_THREADS));
+}
+
 static cnpc_status sums_counted(const cnpc_mesh_desc* d, const uint32_t* pos, const float* w, int64_t n,
                                 int lmax, double* sums, double* partial, const CountArgs& ca, hipStream_t s) {
-  const int nblocks = (int)std::max<int64_t>(1, std::min<int64_t>(SUMS_BLOCKS, (n + SUMS_THREADS - 1) / SUMS_THREADS));
+  const int nblocks = sums_blocks(n);
   SumsArgs a;
   a.lmax = lmax;
   a.boxsize = d->boxsize;
@@ -1541,14 +1662,18 @@ PaintLayout paint_layout(const cnpc_mesh_desc* d, int64_t ngal, int64_t nran, bo
   const int64_t np = ngal > nran ? ngal : nran;
   const size_t rec = (size_t)np * (weighted ? 16 : 12);
   size_t off = 0;
+  // a mesh of one bucket sorts both catalogs at once (paint_small)
   L.off_rec = off; off = align_up(off + rec);
+  if (L.nbuckets == 1) off = align_up(off + rec);
   L.off_tmp = off; off = align_up(off + (L.nbuckets > 1 ? rec : 0));
   L.off_count[0] = off; off = align_up(off + (size_t)L.ntiles * 4);
   L.off_count[1] = off; off = align_up(off + (size_t)L.ntiles * 4);
   L.off_partial = off; off = align_up(off + (size_t)BUCKET_BLOCKS_MAX * CNPC_SUMS_LEN * 8);
   L.off_sums = off; off = align_up(off + (size_t)2 * CNPC_SUMS_LEN * 8);
-  L.off_start = off; off = align_up(off + (size_t)L.ntiles * 4);
-  L.off_cursor = off; off = align_up(off + (size_t)L.ntiles * 4);
+  const size_t slots = L.nbuckets == 1 ? 2 * SMALL_TILES : (size_t)L.ntiles;
+  L.off_start = off; off = align_up(off + slots * 4);
+  L.off_cursor = off; off = align_up(off + slots * 4);
+  L.off_hist = off; off = align_up(off + (L.nbuckets == 1 ? (size_t)2 * SUMS_BLOCKS * SMALL_TILES * 4 : 0));
   L.off_bcur = off; off = align_up(off + (size_t)L.nbuckets * 4);
   for (int k = 0; k < L.nsets; ++k) {
     L.off_blocks[k] = off;
@@ -1628,34 +1753,103 @@ static cnpc_status launch_partition(const uint32_t* pos, const float* w, const R
   return CNPC_OK;
 }
 
-// Tile painting of tile-sorted records (rec, start, count of set set0).
+// Tile painting of tile-sorted records: ncat catalogs in one launch
 template <typename T, int RS>
-static cnpc_status paint_sorted(const cnpc_mesh_desc* d, bool weighted, int set0, unsigned char* ws,
-                                const PaintLayout& L, hipStream_t s) {
+static cnpc_status launch_paint_tiles(const cnpc_mesh_desc* d, bool weighted, int ncat, const PaintCats<T, RS>& pc,
+                                      const PaintLayout& L, hipStream_t s) {
   const TileGeom g = tile_geom(d);
-  uint32_t* count = reinterpret_cast<uint32_t*>(ws + L.off_count[set0]);
-  uint32_t* start = reinterpret_cast<uint32_t*>(ws + L.off_start);
-  Rec<RS>* rec = reinterpret_cast<Rec<RS>*>(ws + L.off_rec);
   kt_begin(CNPC_KT_PAINT, s);
   if constexpr (sizeof(T) == 4 && RS == 3) {
     // unit weights: w^2 = w, the second power's blocks are painted alike
     for (int pw = 0; pw < (weighted ? 2 : 1); ++pw) {
-      T* blocks = reinterpret_cast<T*>(ws + L.off_blocks[set0 + 2 * pw]);
+      PaintCats<T, RS> p = pc;
+      for (int c = 0; c < ncat; ++c) p.blocks[c] = pc.blocks[c + 2 * pw];
       hipLaunchKernelGGL((d->assign == CNPC_TSC ? k_paint_tiles_u32<CNPC_TSC> : k_paint_tiles_u32<CNPC_CIC>),
-                         dim3(L.ntiles), dim3(PAINT32_THREADS), 0, s, rec, start, count, g, L.nphase,
-                         packs_records(true, 3, g.shift), blocks);
+                         dim3(L.ntiles, (unsigned)ncat), dim3(PAINT32_THREADS), 0, s, p, g, L.nphase,
+                         packs_records(true, 3, g.shift));
     }
   } else {
     const int npow = weighted ? 2 : 1;
-    T* b1 = reinterpret_cast<T*>(ws + L.off_blocks[set0]);
-    T* b2 = weighted ? reinterpret_cast<T*>(ws + L.off_blocks[set0 + 2]) : nullptr;
     hipLaunchKernelGGL((d->assign == CNPC_TSC ? k_paint_tiles<T, CNPC_TSC, RS> : k_paint_tiles<T, CNPC_CIC, RS>),
-                       dim3((unsigned)(L.ntiles * L.nphase * npow)), dim3(1024), 0, s, rec, start, count, g, L.nphase,
-                       npow, b1, b2);
+                       dim3((unsigned)(L.ntiles * L.nphase * npow), (unsigned)ncat), dim3(1024), 0, s, pc, g, L.nphase,
+                       npow);
   }
   kt_end(CNPC_KT_PAINT, s);
   CNPC_HIP(hipGetLastError());
   return CNPC_OK;
+}
+
+// the records of set set0 (rec, start of the layout, its count)
+template <typename T, int RS>
+static cnpc_status paint_sorted(const cnpc_mesh_desc* d, bool weighted, int set0, unsigned char* ws,
+                                const PaintLayout& L, hipStream_t s) {
+  PaintCats<T, RS> pc{};
+  pc.rec[0] = reinterpret_cast<const Rec<RS>*>(ws + L.off_rec);
+  pc.start[0] = reinterpret_cast<const uint32_t*>(ws + L.off_start);
+  pc.count[0] = reinterpret_cast<const uint32_t*>(ws + L.off_count[set0]);
+  pc.blocks[0] = reinterpret_cast<T*>(ws + L.off_blocks[set0]);
+  if (weighted) pc.blocks[2] = reinterpret_cast<T*>(ws + L.off_blocks[set0 + 2]);
+  return launch_paint_tiles<T, RS>(d, weighted, 1, pc, L, s);
+}
+
+// Meshes of one tile bucket (N <= 64), both catalogs with weights or both
+// without: sums and tile histograms of both catalogs, their reductions with the
+// scan and the norms, the sort and the painting, one launch each (13 launches
+// with a catalog at a time).  Such passes are bound by the launches: P_0,2 on 32^3
+// 171 us with 31 launches before, 146 with 21; P_0,2,4 on 64^3 225 before, 193.
+template <typename T, int RS>
+static cnpc_status paint_small(const cnpc_mesh_desc* d, const uint32_t* const* pos, const float* const* w,
+                               const int64_t* n, bool weighted, int lmax, double* const* sums, double* norms,
+                               unsigned char* ws, const PaintLayout& L, hipStream_t s) {
+  const TileGeom g = tile_geom(d);
+  SmallPair sp;
+  PaintCats<T, RS> pc{};
+  int nblk = 1;
+  int64_t nmax = 1;
+  const size_t rec = ((size_t)std::max(n[0], n[1]) * RS * 4 + 255) & ~(size_t)255;
+  for (int c = 0; c < 2; ++c) {
+    SmallCat& k = sp.c[c];
+    k.pos = pos[c];
+    k.w = w[c];
+    k.n = n[c];
+    k.nblk = sums_blocks(n[c]);
+    k.partial = reinterpret_cast<double*>(ws + L.off_partial) + (size_t)c * SUMS_BLOCKS * CNPC_SUMS_LEN;
+    k.hist = reinterpret_cast<uint32_t*>(ws + L.off_hist) + (size_t)c * SUMS_BLOCKS * SMALL_TILES;
+    k.count = reinterpret_cast<uint32_t*>(ws + L.off_count[c]);
+    k.start = reinterpret_cast<uint32_t*>(ws + L.off_start) + c * SMALL_TILES;
+    k.cursor = reinterpret_cast<uint32_t*>(ws + L.off_cursor) + c * SMALL_TILES;
+    k.rec = ws + L.off_rec + c * rec;
+    k.sums = sums[c];
+    pc.rec[c] = reinterpret_cast<const Rec<RS>*>(k.rec);
+    pc.start[c] = k.start;
+    pc.count[c] = k.count;
+    pc.blocks[c] = reinterpret_cast<T*>(ws + L.off_blocks[c]);
+    if (weighted) pc.blocks[c + 2] = reinterpret_cast<T*>(ws + L.off_blocks[c + 2]);
+    nblk = std::max(nblk, k.nblk);
+    nmax = std::max(nmax, n[c]);
+  }
+  SumsArgs a;
+  a.lmax = lmax;
+  a.boxsize = d->boxsize;
+  for (int i = 0; i < 3; ++i) { a.obs[i] = d->observer[i]; a.los[i] = d->los[i]; }
+  a.global_los = d->los_mode == CNPC_LOS_GLOBAL;
+  kt_begin(CNPC_KT_SUMS, s);
+  hipLaunchKernelGGL((lmax >= 4 ? k_catalog_sums2<4> : lmax >= 2 ? k_catalog_sums2<2> : k_catalog_sums2<0>),
+                     dim3((unsigned)nblk, 2), dim3(SUMS_THREADS), L.ntiles * 4, s, sp, a, g, L.ntiles);
+  kt_end(CNPC_KT_SUMS, s);
+  CNPC_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_small_scan, dim3(3), dim3(1024), 0, s, sp, L.ntiles, n[0], d->boxsize, norms);
+  CNPC_HIP(hipGetLastError());
+  // chunks of 4 particles per thread once they fill the CUs, of 1 below that
+  const int per = nmax >= (int64_t)1024 * 4 * 256 ? 4 : 1;
+  const unsigned pblk = (unsigned)((nmax + 1024 * per - 1) / (1024 * per));
+  const size_t lds = partition_lds(per, RS, L.ntiles, 1024);
+  kt_begin(CNPC_KT_SORT, s);
+  hipLaunchKernelGGL((per == 4 ? k_partition2<RS, 4> : k_partition2<RS, 1>), dim3(pblk, 2), dim3(1024), lds, s, sp, g,
+                     L.ntiles);
+  kt_end(CNPC_KT_SORT, s);
+  CNPC_HIP(hipGetLastError());
+  return launch_paint_tiles<T, RS>(d, weighted, 2, pc, L, s);
 }
 
 template <typename T, int RS>
@@ -1861,7 +2055,12 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   return paint_sorted<T, RS>(d, weighted, set0, ws, L, s);
 }
 
-// fused: sums_lmax >= 0 selects the fused bucket pass (catalog sums into
+// the one-bucket route of paint_small: both catalogs weighted or both not
+static bool paint_is_small(const PaintLayout& L, const float* gw, const float* rw) {
+  return L.nbuckets == 1 && (gw != nullptr) == (rw != nullptr);
+}
+
+// fused: sums_lmax >= 0 selects paint_small or the fused bucket pass (catalog sums into
 // gs / rs, and with form_norms the norms after both catalogs); counted: tile
 // counts already taken.
 template <typename T>
@@ -1879,9 +2078,17 @@ static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const 
   fa.nt = L.nt;
   fa.nphase = L.nphase;
   fa.nsets = L.nsets;
+  const bool small = sums_lmax >= 0 && paint_is_small(L, gw, rw);
+  if (small) {
+    double* sums_c[2] = {gs, rs};
+    double* nm = form_norms ? const_cast<double*>(norms) : nullptr;
+    if (weighted) CNPC_TRY((paint_small<T, 4>(d, cpos, cw, cn, true, sums_lmax, sums_c, nm, ws, L, s)));
+    else CNPC_TRY((paint_small<T, 3>(d, cpos, cw, cn, false, sums_lmax, sums_c, nm, ws, L, s)));
+  }
   for (int c = 0; c < 2; ++c) {
     for (int pw = 0; pw < (weighted ? 2 : 1); ++pw)
       fa.blocks[c + 2 * pw] = reinterpret_cast<T*>(ws + L.off_blocks[c + 2 * pw]);
+    if (small) continue;
     double* sums_c = c == 0 ? gs : rs;
     if (sums_lmax >= 0 && cw[c])
       CNPC_TRY((fused_sort_and_paint<T, 4>(d, cpos[c], cw[c], cn[c], c, weighted, sums_lmax, sums_c, ws, L, s)));
@@ -1892,7 +2099,7 @@ static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const 
     else
       CNPC_TRY((sort_and_paint<T, 3>(d, cpos[c], nullptr, cn[c], c, weighted, counted, ws, L, s)));
   }
-  if (sums_lmax >= 0 && form_norms) CNPC_TRY(launch_norms(d, gs, rs, ngal, const_cast<double*>(norms), s));
+  if (sums_lmax >= 0 && form_norms && !small) CNPC_TRY(launch_norms(d, gs, rs, ngal, const_cast<double*>(norms), s));
   if (!fold) return CNPC_OK;
   const int z2 = L.nt >= 2 ? 2 : 1;
   const int64_t nb = (int64_t)L.nphase * L.nt * L.nt * (L.nt / z2);
@@ -1915,9 +2122,9 @@ cnpc_status launch_paint(const cnpc_mesh_desc* d, const uint32_t* gpos, const fl
   }
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
   // several buckets: the bucket pass (one read of the catalog for the tile
-  // counts and the first sort step; its l = 0 sums are not used here), else
-  // the tile count in a read of its own
-  const int lm = L.nbuckets > 1 && tune_value(CNPC_TUNE_SORT_FUSED) != 1 ? 0 : -1;
+  // counts and the first sort step); one bucket: paint_small (the l = 0 sums of
+  // both are not used here); else the tile count in a read of its own
+  const int lm = (L.nbuckets > 1 ? tune_value(CNPC_TUNE_SORT_FUSED) != 1 : paint_is_small(L, gw, rw)) ? 0 : -1;
   double* sums = reinterpret_cast<double*>(w + L.off_sums);
   if (d->dtype == CNPC_F64)
     return paint_t<double>(d, gpos, gw, ngal, rpos, rw, nran, norms, (double*)delta, (double*)noise, w,
@@ -2007,7 +2214,7 @@ cnpc_status launch_paint_fkp(const cnpc_mesh_desc* d, const uint32_t* gpos, cons
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
   double* gs_ = gsums ? gsums : reinterpret_cast<double*>(w + L.off_sums);
   double* rs_ = rsums ? rsums : reinterpret_cast<double*>(w + L.off_sums) + CNPC_SUMS_LEN;
-  if (L.nbuckets > 1 && tune_value(CNPC_TUNE_SORT_FUSED) != 1) {
+  if (L.nbuckets > 1 ? tune_value(CNPC_TUNE_SORT_FUSED) != 1 : paint_is_small(L, gw, rw)) {
     if (d->dtype == CNPC_F64)
       return paint_t<double>(d, gpos, gw, ngal, rpos, rw, nran, norms, (double*)delta, (double*)noise, w, L,
                              false, s, sums_lmax, gs_, rs_);

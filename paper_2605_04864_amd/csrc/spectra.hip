@@ -1474,10 +1474,12 @@ __global__ void k_zero_f64(double* p, int64_t n) {
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = 0.0;
 }
-__global__ void k_zero_i64(int64_t* p, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0;
+// the shell accumulators and mode counts of k_bin
+__global__ void k_bin_zero(double* acc, int64_t n, int64_t* cnt, int64_t m) {
+  for (int64_t i = threadIdx.x; i < n + m; i += blockDim.x) {
+    if (i < n) acc[i] = 0.0;
+    else cnt[i - n] = 0;
+  }
 }
 
 // acc [nbins][nacc] sums -> shell means
@@ -1519,9 +1521,7 @@ static cnpc_status bin_t(const cnpc_mesh_desc* d, const int64_t* thr, int nbins,
   for (int q = 0; q < nself; ++q) a.self_ell[q] = self_ells[q];
   const int nacc = npairs + nself + 1;
   const int64_t nacc_tot = (int64_t)nbins * nacc;
-  hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(256), 0, s, acc, nacc_tot);
-  CNPC_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_zero_i64, dim3(1), dim3(256), 0, s, nmodes, (int64_t)nbins);
+  hipLaunchKernelGGL(k_bin_zero, dim3(1), dim3(256), 0, s, acc, nacc_tot, nmodes, (int64_t)nbins);
   CNPC_HIP(hipGetLastError());
   const int64_t bsz = (int64_t)4 * band * band * band;
   const unsigned g = (unsigned)std::min<int64_t>((bsz + 255) / 256, 2048);
