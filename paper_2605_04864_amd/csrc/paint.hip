@@ -1442,6 +1442,108 @@ __global__ void __launch_bounds__(512) k_fold_tiles(FoldArgs<T> fa, const double
   if (noise) store16<T>(noise + idx, q);
 }
 
+// Fold for meshes of 256 and 512: a workgroup takes RW = 256 / nt rows (x, y) of a
+// tile column, one lane per row and z tile (lane (cy, tz): 16 lanes read rows that
+// are consecutive in a block), so that the z halos stay inside the workgroup:
+// summed rows are staged in LDS, the halo values added there after a barrier (one
+// writer per node), and whole mesh rows stored.  A lane without a y halo reads its
+// own row for the y-neighbour sources and weighs them by zero, so that no load
+// sits in a divergent branch.  Same sums as k_fold_tiles up to rounding.  Bound by
+// HBM: 512^3 FP32, both meshes, 5.8 GB, 1530 us with a tile pair's rows per workgroup
+// (k_fold_tiles) before, 1199 here (4.8 TB/s); 512^3 FP64 one mesh 3161 before, 2557
+// here; 256^3 FP64 one mesh 328 before, 275 here, both 428 before, 328 here.
+template <typename T, int NT_>
+__global__ void __launch_bounds__(256) k_fold_rows(FoldArgs<T> fa, const double* __restrict__ norms,
+                                                   T* __restrict__ delta, T* __restrict__ noise) {
+  constexpr int N = 16 * NT_, RW = 256 / NT_;  // nodes per row, rows per workgroup
+  static_assert(RW <= 16, "rows of one x node");
+  constexpr int RS = N + NT_;                  // staged row stride (one of padding per 16)
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cx<T>* stage = reinterpret_cast<cx<T>*>(smem_raw);  // [RW][RS]
+  // workgroups go to the 8 XCDs in turn: each XCD takes a contiguous range of
+  // tile columns, so the blocks and halo rows they share meet in one L2
+  int b = (int)((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+  const int row0 = (b % (256 / RW)) * RW;
+  b /= 256 / RW;
+  const int ty = b % NT_;
+  b /= NT_;
+  const int tx = b % NT_;
+  const int ph = b / NT_;
+  const int tz = threadIdx.x / RW, lr = threadIdx.x % RW;
+  const int c_x = (row0 + lr) >> 4, cy = (row0 + lr) & 15;
+  const double alpha = norms[CNPC_NORM_ALPHA];
+  T cd[4] = {T(0), T(0), T(0), T(0)}, cn[4] = {T(0), T(0), T(0), T(0)};
+  if (fa.nsets == 2) {
+    cd[0] = T(1); cd[1] = T(-alpha); cn[0] = T(1); cn[1] = T(alpha * alpha);
+  } else {
+    cd[0] = T(1); cd[1] = T(-alpha); cn[2] = T(1); cn[3] = T(alpha * alpha);
+  }
+  // the workgroup's RW <= 16 rows share x node c_x: hx is uniform
+  const bool hx = c_x <= 1 || c_x == 15, hy = cy <= 1 || cy == 15;
+  const int txn = c_x <= 1 ? (tx - 1 + NT_) % NT_ : (tx + 1) % NT_;
+  const int tyn = cy <= 1 ? (ty - 1 + NT_) % NT_ : (ty + 1) % NT_;
+  const int lxn = c_x <= 1 ? c_x + 17 : 0, lyn = cy <= 1 ? cy + 17 : 0;
+  const int64_t bst = (int64_t)fa.nphase * BSTRIDE;
+  int64_t o[4];  // source k = 2 a + c (a: x neighbour, c: y neighbour)
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const bool a = k >> 1, c = (k & 1) && hy;
+    o[k] = (((int64_t)(a ? txn : tx) * NT_ + (c ? tyn : ty)) * NT_ + tz) * bst + (int64_t)ph * BSTRIDE +
+           ((a ? lxn : c_x + 1) * BW + (c ? lyn : cy + 1)) * BW;
+  }
+  const T fy = hy ? T(1) : T(0);
+  T d[19], q[19];
+#pragma unroll
+  for (int e = 0; e < 19; ++e) d[e] = q[e] = T(0);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    if (s >= fa.nsets) break;
+    const T* __restrict__ bl = fa.blocks[s];
+    T v[19], u[19];
+    load16<T>(bl + o[0], v);
+    v[16] = bl[o[0] + 16]; v[17] = bl[o[0] + 17]; v[18] = bl[o[0] + 18];
+    load16<T>(bl + o[1], u);
+    u[16] = bl[o[1] + 16]; u[17] = bl[o[1] + 17]; u[18] = bl[o[1] + 18];
+#pragma unroll
+    for (int e = 0; e < 19; ++e) v[e] += fy * u[e];
+    if (hx) {
+      load16<T>(bl + o[2], u);
+      u[16] = bl[o[2] + 16]; u[17] = bl[o[2] + 17]; u[18] = bl[o[2] + 18];
+#pragma unroll
+      for (int e = 0; e < 19; ++e) v[e] += u[e];
+      load16<T>(bl + o[3], u);
+      u[16] = bl[o[3] + 16]; u[17] = bl[o[3] + 17]; u[18] = bl[o[3] + 18];
+#pragma unroll
+      for (int e = 0; e < 19; ++e) v[e] += fy * u[e];
+    }
+#pragma unroll
+    for (int e = 0; e < 19; ++e) {
+      d[e] += cd[s] * v[e];
+      q[e] += cn[s] * v[e];
+    }
+  }
+  // staged node (row, z) at row * RS + z + z / 16
+  cx<T>* srow = stage + lr * RS;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) srow[17 * tz + e] = cx<T>{d[e], q[e]};
+  __syncthreads();
+  {
+    cx<T>* up = srow + 17 * ((tz + 1) % NT_);
+    cx<T>* lo = srow + 17 * ((tz + NT_ - 1) % NT_) + 15;
+    up[0] = cadd(up[0], cx<T>{d[16], q[16]});
+    up[1] = cadd(up[1], cx<T>{d[17], q[17]});
+    *lo = cadd(*lo, cx<T>{d[18], q[18]});
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < RW * N; i += 256) {
+    const int r = i / N, z = i % N, gr = row0 + r;
+    const cx<T> v = stage[r * RS + z + (z >> 4)];
+    const int64_t idx = (((int64_t)ph * N + 16 * tx + (gr >> 4)) * N + 16 * ty + (gr & 15)) * N + z;
+    delta[idx] = v.x;
+    if (noise) noise[idx] = v.y;
+  }
+}
+
 // Fold fused with the z pass of the de-interlacing transforms (N = 256: 16
 // z-tiles, one z-row = one row_fft_rr of 16 lanes).  A workgroup takes the 16
 // node rows (x, y = 16 ty + cy) of one x node x = 16 tx + cx of the tile
@@ -2101,10 +2203,24 @@ static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const 
   }
   if (sums_lmax >= 0 && form_norms && !small) CNPC_TRY(launch_norms(d, gs, rs, ngal, const_cast<double*>(norms), s));
   if (!fold) return CNPC_OK;
-  const int z2 = L.nt >= 2 ? 2 : 1;
-  const int64_t nb = (int64_t)L.nphase * L.nt * L.nt * (L.nt / z2);
   kt_begin(CNPC_KT_FOLD, s);
-  hipLaunchKernelGGL((k_fold_tiles<T>), dim3((unsigned)nb), dim3(256 * z2), 0, s, fa, norms, delta, noise);
+  auto rows = [&](auto ntc) {
+    constexpr int NT_ = decltype(ntc)::value, RW = 256 / NT_;
+    const unsigned nb = (unsigned)(L.nphase * NT_ * NT_ * (256 / RW));  // a multiple of 8
+    hipLaunchKernelGGL((k_fold_rows<T, NT_>), dim3(nb), dim3(256), sizeof(cx<T>) * RW * 17 * NT_, s, fa, norms, delta,
+                       noise);
+  };
+  // 256, 512: whole rows; smaller meshes keep the z-tile pairs (128^3 FP64 74 us, 89
+  // in rows), where more workgroups than rows fill the CUs
+  if (L.nt == 16) {
+    rows(std::integral_constant<int, 16>());
+  } else if (L.nt == 32) {
+    rows(std::integral_constant<int, 32>());
+  } else {
+    const int z2 = L.nt >= 2 ? 2 : 1;
+    const int64_t nb = (int64_t)L.nphase * L.nt * L.nt * (L.nt / z2);
+    hipLaunchKernelGGL((k_fold_tiles<T>), dim3((unsigned)nb), dim3(256 * z2), 0, s, fa, norms, delta, noise);
+  }
   kt_end(CNPC_KT_FOLD, s);
   CNPC_HIP(hipGetLastError());
   return CNPC_OK;

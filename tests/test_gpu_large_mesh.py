@@ -161,3 +161,38 @@ def test_deinterlace_fused_x_pass(n, band, dtype):
     tol = 1e-12 if dtype == L.F64 else 2e-6
     for a, b in zip(out[0], out[1]):
         assert float((a - b).abs().max()) <= tol * float(b.abs().max())
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("dtype", [L.F32, L.F64])
+@pytest.mark.parametrize("n", [256, 512])
+def test_fold_rows_exact_on_nodes(n, dtype, weighted):
+    """Row fold on a sparse catalog of particles exactly on nodes, at tile faces and
+    the box's periodic faces, with weights of powers of two and alpha = 1: every
+    contribution is a multiple of 2^-13, so both meshes are exact in either type."""
+    d = cn.mesh_desc(n, 2000.0, assign=L.TSC, interlace=True, dtype=dtype)
+    shift = 32 - int(np.log2(n))
+    rng = np.random.default_rng(9)
+    faces = np.array([0, 1, 14, 15, 16, 17, n // 2 - 1, n // 2, n - 17, n - 16, n - 2, n - 1])
+    m = 900
+    w = rng.choice(np.array([0.5, 1.0, 2.0], dtype=np.float32), m)
+    cat = [((rng.choice(faces, (3, m)).astype(np.uint64)) << np.uint64(shift)).astype(np.uint32) for _ in range(2)]
+    g, r = (torch.from_numpy(x).cuda() for x in cat)
+    wt = (torch.from_numpy(w).cuda(), torch.from_numpy(w[::-1].copy()).cuda()) if weighted else (None, None)
+    norms, delta, nmesh, _, _ = pl.paint_fkp(d, g, r, *wt)
+    assert float(norms[L.NORM_ALPHA]) == 1.0
+    # TSC of a particle on node c: phase A nodes c - 1 .. c + 1; phase B (u - 1/2) nodes c - 1, c
+    sten = (((-1, 0.125), (0, 0.75), (1, 0.125)), ((-1, 0.5), (0, 0.5)))
+    for ph in range(2):
+        ref = torch.zeros((2, n ** 3), dtype=torch.float64, device="cuda")
+        for pos, ww, sign in ((cat[0], wt[0], 1.0), (cat[1], wt[1], -1.0)):
+            c = torch.from_numpy((pos >> shift).astype(np.int64)).cuda()
+            ww = ww.double() if weighted else torch.ones(m, dtype=torch.float64, device="cuda")
+            for ox, vx in sten[ph]:
+                for oy, vy in sten[ph]:
+                    for oz, vz in sten[ph]:
+                        idx = (((c[0] + ox) % n) * n + (c[1] + oy) % n) * n + (c[2] + oz) % n
+                        ref[0].index_add_(0, idx, sign * ww * (vx * vy * vz))
+                        ref[1].index_add_(0, idx, ww * ww * (vx * vy * vz))
+        assert torch.equal(delta[ph].reshape(-1).double(), ref[0])
+        assert torch.equal(nmesh[ph].reshape(-1).double(), ref[1])
