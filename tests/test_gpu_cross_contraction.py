@@ -65,3 +65,25 @@ def test_sugiyama_tiles(l1, l2, lm, nb):
         L.check(L.lib.cnpc_sugiyama(plan.handle, L.ptr(s[0]), L.ptr(s[1:]) if lm else None, None, L.ptr(norms),
                                     L.ptr(raw), L.ptr(shot), L.ptr(val), L.ptr(ws), ws.numel(), L.stream_handle()))
     _both(128, nb, lambda d, b, p, sc: pl.SugiPlan(d, b, l1, l2, lm, p), call, 1 + 2 * lm + 1)
+
+
+# FP64 row-per-pair contraction with the next chunk in registers (up to 40 fields
+# at 128 points a chunk, 26 at 256) and without (more fields)
+@pytest.mark.parametrize("ell,nb", [(0, 13), (0, 26), (2, 13), (2, 14), (2, 20), (2, 21)])
+def test_scoccimarro_prefetch_edges(ell, nb):
+    kf = 2.0 * np.pi / 1000.0
+    bins = cn.kbins(0.0, 1.01 * kf, nb)
+    norms = torch.ones(L.NORMS_LEN, dtype=torch.float64, device="cuda")
+    res = {}
+    for dt, prec in ((L.F64, L.PREC_F64), (L.F32, L.PREC_F32)):
+        d = cn.mesh_desc(64, 1000.0, dtype=dt)
+        sc = pl.Scratch()
+        plan = pl.BispecPlan(d, bins, L.EST_SCOCCIMARRO, ell, prec, sc)
+        s = _spectra(64, plan.band, 2, nb).to(pl._TORCH_DT[dt]).contiguous()
+        raw, shot, val = (torch.zeros(plan.nconf, dtype=torch.float64, device="cuda") for _ in range(3))
+        ws = sc.get(plan.ws_bytes)
+        L.check(L.lib.cnpc_bispectrum(plan.handle, L.ptr(s[0]), L.ptr(s[1]) if ell else None, None, L.ptr(norms),
+                                      L.ptr(raw), L.ptr(shot), L.ptr(val), L.ptr(ws), ws.numel(), L.stream_handle()))
+        torch.cuda.synchronize()
+        res[dt] = raw.cpu().numpy()
+    assert np.max(np.abs(res[L.F32] - res[L.F64])) < 1e-5 * np.max(np.abs(res[L.F64]))
