@@ -1343,23 +1343,33 @@ cnpc_status launch_deinterlace(const cnpc_mesh_desc* d, int band, const void* me
 }
 
 // --------------------------------------------------------- F_l assembly --
+// W(k) is the product of three values of a table over the band index (one
+// sinpi per axis and mode in FP64 held the kernel to a third of the copy rate),
+// formed once per workgroup: ASM_BLOCKS workgroups at most walk the band.  Band
+// 128, FP32, l = 0, 0, 2: 300 us before, 135 here.
+constexpr int ASM_BLOCKS = 2048;
 template <typename T>
 __global__ void __launch_bounds__(256) k_assemble(int n, int m, int ell, int assign,
                                                   const cx<T>* __restrict__ spec0,
                                                   const cx<T>* __restrict__ ylm, cx<T>* __restrict__ F) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* win = reinterpret_cast<double*>(smem_raw);  // [2m] window of band index j
+  for (int j = threadIdx.x; j < 2 * m; j += 256) win[j] = window_1d(band_freq(j, m), n, assign);
+  __syncthreads();
   const int64_t bsz = (int64_t)4 * m * m * m;
+  const int lm = 31 - __clz(m);  // m is a power of two
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < bsz;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const int kz = (int)(i % m);
-    const int jy = (int)((i / m) % (2 * m));
-    const int jx = (int)(i / ((int64_t)2 * m * m));
+    const int kz = (int)(i & (m - 1));
+    const int jy = (int)(i >> lm) & (2 * m - 1);
+    const int jx = (int)(i >> (2 * lm + 1));
     const int nx = band_freq(jx, m), ny = band_freq(jy, m), nz = kz;
     const int64_t n2 = (int64_t)nx * nx + (int64_t)ny * ny + (int64_t)nz * nz;
     if (n2 == 0 || nx == -(n / 2) || ny == -(n / 2)) {
       F[i] = cx<T>{T(0), T(0)};
       continue;
     }
-    const double W = window_1d(nx, n, assign) * window_1d(ny, n, assign) * window_1d(nz, n, assign);
+    const double W = win[jx] * win[jy] * win[kz];
     if (ell == 0) {
       const cx<T> v = spec0[i];
       F[i] = cx<T>{T(v.x / W), T(v.y / W)};
@@ -1382,81 +1392,130 @@ __global__ void __launch_bounds__(256) k_assemble(int n, int m, int ell, int ass
 cnpc_status launch_assemble(const cnpc_mesh_desc* d, int band, int ell, const void* spec0,
                             const void* ylm, void* F, hipStream_t s) {
   const int64_t bsz = (int64_t)4 * band * band * band;
-  const unsigned g = (unsigned)std::min<int64_t>((bsz + 255) / 256, 65536);
+  const unsigned g = (unsigned)std::min<int64_t>((bsz + 255) / 256, ASM_BLOCKS);
   if (d->dtype == CNPC_F64)
-    hipLaunchKernelGGL((k_assemble<double>), dim3(g), dim3(256), 0, s, d->n, band, ell, d->assign,
+    hipLaunchKernelGGL((k_assemble<double>), dim3(g), dim3(256), sizeof(double) * 2 * band, s, d->n, band, ell, d->assign,
                        (const cx<double>*)spec0, (const cx<double>*)ylm, (cx<double>*)F);
   else
-    hipLaunchKernelGGL((k_assemble<float>), dim3(g), dim3(256), 0, s, d->n, band, ell, d->assign,
+    hipLaunchKernelGGL((k_assemble<float>), dim3(g), dim3(256), sizeof(double) * 2 * band, s, d->n, band, ell, d->assign,
                        (const cx<float>*)spec0, (const cx<float>*)ylm, (cx<float>*)F);
   CNPC_HIP(hipGetLastError());
   return CNPC_OK;
 }
 
 // ---------------------------------------------------------------- binning --
-template <typename T>
-__global__ void __launch_bounds__(256) k_bin(BinArgs<T> a, const double* __restrict__ norms,
+// A thread takes `run` consecutive kz of a row (nx, ny), along which |n|^2 grows
+// (8 from band 128 up, 4 at 64, 2 below, where longer runs would leave CUs idle), and adds its shell sums to LDS when the bin changes: a shell holds several
+// neighbouring kz, whose atomics would meet on one address.  Windows and alias
+// sums come from tables over the band index.  NP: accumulators per thread
+// (npairs + nself <= NP).  Band 64, 2 pairs and a self term, FP64: 56 us with
+// an atomic per mode and FP64 trigonometry per mode before, 37 here; band 128 302 before,
+// 254 here.
+static int bin_run(int m) { return std::min(m, m >= 128 ? 8 : m == 64 ? 4 : 2); }
+template <typename T, int NP>
+__global__ void __launch_bounds__(256) k_bin(BinArgs<T> a, int run, const double* __restrict__ norms,
                                              double* __restrict__ acc_out,
                                              unsigned long long* __restrict__ cnt_out) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int nacc = a.npairs + a.nself + 1;  // + sum |k|
+  const int nq = a.npairs + a.nself, nacc = nq + 1;  // + sum |k|
+  const int m = a.m, n = a.n;
   double* acc = reinterpret_cast<double*>(smem_raw);
   unsigned long long* cnt = reinterpret_cast<unsigned long long*>(acc + (int64_t)a.nbins * nacc);
+  double* win = reinterpret_cast<double*>(cnt + a.nbins);  // [2m] each, with self terms only
+  double *al = win + 2 * m, *at = al + 2 * m;
   for (int i = threadIdx.x; i < a.nbins * nacc; i += blockDim.x) acc[i] = 0.0;
   for (int i = threadIdx.x; i < a.nbins; i += blockDim.x) cnt[i] = 0ull;
+  if (a.nself)
+    for (int j = threadIdx.x; j < 2 * m; j += blockDim.x) {
+      win[j] = window_1d(band_freq(j, m), n, a.assign);
+      alias_1d(band_freq(j, m), n, a.assign, &al[j], &at[j]);
+    }
   __syncthreads();
-  const int m = a.m, n = a.n;
-  const int64_t bsz = (int64_t)4 * m * m * m;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < bsz;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int kz = (int)(i % m);
-    const int jy = (int)((i / m) % (2 * m));
-    const int jx = (int)(i / ((int64_t)2 * m * m));
-    const int nx = band_freq(jx, m), ny = band_freq(jy, m), nz = kz;
-    if (nx == -(n / 2) || ny == -(n / 2) || nz == n / 2) continue;
-    const int64_t n2 = (int64_t)nx * nx + (int64_t)ny * ny + (int64_t)nz * nz;
-    if (n2 == 0 || n2 < a.thr[0] || n2 >= a.thr[a.nbins]) continue;
-    int lo = 0, hi = a.nbins;  // thr[lo] <= n2 < thr[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (n2 >= a.thr[mid]) lo = mid; else hi = mid;
-    }
-    const int b = lo;
-    const double wgt = nz == 0 ? 1.0 : 2.0;
-    double* ab = acc + b * nacc;
-    for (int q = 0; q < a.npairs; ++q) {
-      const cx<T> fa = a.pa[q][i], fb = a.pb[q][i];
-      // Re or Im of F_a F_b^*; for an anti-Hermitian product (odd l) the
-      // k and -k halves carry the same imaginary part, so the half-grid
-      // weights apply to both
-      const double v = ((a.imag >> q) & 1u) ? (double)fa.y * (double)fb.x - (double)fa.x * (double)fb.y
-                                            : (double)fa.x * (double)fb.x + (double)fa.y * (double)fb.y;
-      atomicAdd(&ab[q], wgt * v);
-    }
-    if (a.nself) {
-      const double kn = sqrt((double)n2);
-      const double ux = nx / kn, uy = ny / kn, uz = nz / kn;
-      double cxs, ctx, cys, cty, czs, ctz;
-      alias_1d(nx, n, a.assign, &cxs, &ctx);
-      alias_1d(ny, n, a.assign, &cys, &cty);
-      alias_1d(nz, n, a.assign, &czs, &ctz);
-      const double C = a.interlace ? 0.5 * (cxs * cys * czs + ctx * cty * ctz) : cxs * cys * czs;
-      const double W = window_1d(nx, n, a.assign) * window_1d(ny, n, a.assign) *
-                       window_1d(nz, n, a.assign);
-      const double cw = C / (W * W);
-      for (int q = 0; q < a.nself; ++q) {
-        const int l = a.self_ell[q];
-        const int base = l == 0 ? 0 : (l == 2 ? 1 : 4);
-        double re[5], im[5];
-        racah_ylm<double>(l, ux, uy, uz, re, im);
-        const double* sb = norms + CNPC_NORM_SBARLM + 2 * base;
-        double v = re[0] * sb[0] - im[0] * sb[1];
-        for (int mm = 1; mm <= l; ++mm) v += 2.0 * (re[mm] * sb[2 * mm] - im[mm] * sb[2 * mm + 1]);
-        atomicAdd(&ab[a.npairs + q], wgt * v * cw);
+  const int per = m / run;
+  const int64_t nruns = (int64_t)4 * m * m * per;
+  for (int64_t ir = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; ir < nruns;
+       ir += (int64_t)gridDim.x * blockDim.x) {
+    const int kz0 = (int)(ir % per) * run;
+    const int64_t row = ir / per;
+    const int jy = (int)(row % (2 * m)), jx = (int)(row / (2 * m));
+    const int nx = band_freq(jx, m), ny = band_freq(jy, m);
+    if (nx == -(n / 2) || ny == -(n / 2)) continue;
+    const int64_t nxy = (int64_t)nx * nx + (int64_t)ny * ny;
+    const int kz1 = kz0 + run - 1;
+    if (nxy + (int64_t)kz1 * kz1 < a.thr[0] || nxy + (int64_t)kz0 * kz0 >= a.thr[a.nbins]) continue;
+    double v[NP], vk = 0.0;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) v[q] = 0.0;
+    unsigned c = 0;
+    int bin = -1;  // bin of the sums in v; thr[bin] <= n^2 < thr[bin + 1]
+    auto flush = [&]() {
+      if (c) {
+        double* ab = acc + bin * nacc;
+#pragma unroll
+        for (int q = 0; q < NP; ++q)
+          if (q < nq) {
+            atomicAdd(&ab[q], v[q]);
+            v[q] = 0.0;
+          }
+        atomicAdd(&ab[nq], vk);
+        atomicAdd(&cnt[bin], (unsigned long long)c);
       }
+      vk = 0.0;
+      c = 0;
+    };
+    for (int kz = kz0; kz <= kz1; ++kz) {
+      const int64_t n2 = nxy + (int64_t)kz * kz;
+      if (kz == n / 2 || n2 == 0 || n2 < a.thr[0]) continue;
+      if (n2 >= a.thr[a.nbins]) break;
+      if (bin < 0) {
+        int lo = 0, hi = a.nbins;
+        while (hi - lo > 1) {
+          const int mid = (lo + hi) >> 1;
+          if (n2 >= a.thr[mid]) lo = mid; else hi = mid;
+        }
+        bin = lo;
+      } else if (n2 >= a.thr[bin + 1]) {
+        flush();
+        do ++bin; while (n2 >= a.thr[bin + 1]);
+      }
+      const int64_t i = row * m + kz;
+      const double wgt = kz == 0 ? 1.0 : 2.0;
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        if (q < a.npairs) {
+          const cx<T> fa = a.pa[q][i], fb = a.pb[q][i];
+          // Re or Im of F_a F_b^*; for an anti-Hermitian product (odd l) the
+          // k and -k halves carry the same imaginary part, so the half-grid
+          // weights apply to both
+          const double f = ((a.imag >> q) & 1u) ? (double)fa.y * (double)fb.x - (double)fa.x * (double)fb.y
+                                                : (double)fa.x * (double)fb.x + (double)fa.y * (double)fb.y;
+          v[q] += wgt * f;
+        }
+      }
+      const double kn = sqrt((double)n2);
+      if (a.nself) {
+        const double ux = nx / kn, uy = ny / kn, uz = kz / kn;
+        const double C = a.interlace ? 0.5 * (al[jx] * al[jy] * al[kz] + at[jx] * at[jy] * at[kz])
+                                     : al[jx] * al[jy] * al[kz];
+        const double W = win[jx] * win[jy] * win[kz];
+        const double cw = C / (W * W);
+        for (int q = 0; q < a.nself; ++q) {
+          const int l = a.self_ell[q];
+          const int base = l == 0 ? 0 : (l == 2 ? 1 : 4);
+          double re[5], im[5];
+          racah_ylm<double>(l, ux, uy, uz, re, im);
+          const double* sb = norms + CNPC_NORM_SBARLM + 2 * base;
+          double f = re[0] * sb[0] - im[0] * sb[1];
+          for (int mm = 1; mm <= l; ++mm) f += 2.0 * (re[mm] * sb[2 * mm] - im[mm] * sb[2 * mm + 1]);
+#pragma unroll
+          for (int e = 0; e < NP; ++e)
+            if (e == a.npairs + q) v[e] += wgt * f * cw;
+        }
+      }
+      vk += wgt * kn;
+      c += kz == 0 ? 1u : 2u;
     }
-    atomicAdd(&ab[a.npairs + a.nself], wgt * sqrt((double)n2));
-    atomicAdd(&cnt[b], (unsigned long long)(nz == 0 ? 1 : 2));
+    flush();
   }
   __syncthreads();
   for (int i = threadIdx.x; i < a.nbins * nacc; i += blockDim.x) {
@@ -1523,12 +1582,15 @@ static cnpc_status bin_t(const cnpc_mesh_desc* d, const int64_t* thr, int nbins,
   const int64_t nacc_tot = (int64_t)nbins * nacc;
   hipLaunchKernelGGL(k_bin_zero, dim3(1), dim3(256), 0, s, acc, nacc_tot, nmodes, (int64_t)nbins);
   CNPC_HIP(hipGetLastError());
-  const int64_t bsz = (int64_t)4 * band * band * band;
-  const unsigned g = (unsigned)std::min<int64_t>((bsz + 255) / 256, 2048);
-  const size_t lds = sizeof(double) * nacc_tot + sizeof(unsigned long long) * nbins;
+  const int run = bin_run(band);
+  const int64_t nruns = (int64_t)4 * band * band * (band / run);
+  const unsigned g = (unsigned)std::min<int64_t>((nruns + 255) / 256, 2048);
+  const size_t lds = sizeof(double) * nacc_tot + sizeof(unsigned long long) * nbins +
+                     (nself ? sizeof(double) * 6 * band : 0);
+  const int nq = npairs + nself;
   kt_begin(CNPC_KT_BIN, s);
-  hipLaunchKernelGGL((k_bin<T>), dim3(g), dim3(256), lds, s, a, norms, acc,
-                     (unsigned long long*)nmodes);
+  hipLaunchKernelGGL((nq <= 4 ? k_bin<T, 4> : nq <= 8 ? k_bin<T, 8> : k_bin<T, MAX_PAIRS + MAX_SELF>), dim3(g), dim3(256),
+                     lds, s, a, run, norms, acc, (unsigned long long*)nmodes);
   kt_end(CNPC_KT_BIN, s);
   CNPC_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_bin_finish, dim3(1), dim3(256), 0, s, acc, nmodes, nbins, npairs, nself,
