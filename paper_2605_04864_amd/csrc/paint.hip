@@ -180,6 +180,9 @@ __device__ __forceinline__ void sums_add(double* acc, uint32_t px, uint32_t py, 
   }
 }
 
+// particles of one of nblk workgroups of a sums pass: consecutive ones
+__host__ __device__ __forceinline__ int64_t sums_range(int64_t n, int nblk) { return (n + nblk - 1) / nblk; }
+
 // Catalog sums of one workgroup, block `blk` of `nblk` (LMAX: Y_lm sums for
 // l <= LMAX, 0, 2 or 4; the others stay zero) into partial[blk], and the tile
 // histogram of its particles: with `hist` stored there (at most 64 tiles), else
@@ -203,8 +206,8 @@ __device__ __forceinline__ void catalog_sums_block(const uint32_t* __restrict__ 
   // U particles per thread and trip: all their loads are issued before any of
   // them is used (fewer for the larger register sets of l > 0)
   constexpr int U = LMAX == 0 ? 4 : (LMAX == 2 ? 2 : 1);
-  const int64_t stride = (int64_t)nblk * blockDim.x;
-  for (int64_t i0 = blk * (int64_t)blockDim.x + threadIdx.x; i0 < n; i0 += U * stride) {
+  const int64_t stride = blockDim.x, c0 = sums_range(n, nblk) * blk, c1 = min(n, c0 + sums_range(n, nblk));
+  for (int64_t i0 = c0 + threadIdx.x; i0 < c1; i0 += U * stride) {
     uint32_t px[U], py[U], pz[U];
     float wv[U];
 #pragma unroll
@@ -212,7 +215,7 @@ __device__ __forceinline__ void catalog_sums_block(const uint32_t* __restrict__ 
       const int64_t i = i0 + u * stride;
       px[u] = py[u] = pz[u] = 0u;
       wv[u] = 1.0f;
-      if (i < n) {
+      if (i < c1) {
         px[u] = ld_stream(pos + i);
         py[u] = ld_stream(pos + n + i);
         pz[u] = ld_stream(pos + 2 * n + i);
@@ -221,7 +224,7 @@ __device__ __forceinline__ void catalog_sums_block(const uint32_t* __restrict__ 
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (i0 + u * stride >= n) break;
+      if (i0 + u * stride >= c1) break;
       if (count) {
         const int t = tile_key(px[u], py[u], pz[u], ca.g);
         if (lds) atomicAdd(&lcount[t], 1u);
@@ -268,8 +271,8 @@ struct SmallCat {
   int64_t n;
   int nblk;           // workgroups of its sums
   double* partial;    // [nblk][CNPC_SUMS_LEN]
-  uint32_t* hist;     // [nblk][SMALL_TILES] tile histograms
-  uint32_t *count, *start, *cursor;  // [ntiles]
+  uint32_t* hist;     // [nblk][SMALL_TILES] tile histograms, then the workgroups' slots
+  uint32_t *count, *start;  // [ntiles]
   void* rec;          // tile-sorted records
   double* sums;
 };
@@ -321,32 +324,48 @@ __global__ void k_norms(const double* __restrict__ gs, const double* __restrict_
 }
 
 // The steps between the sums and the sort of a mesh of one tile bucket, one
-// launch: workgroups 0, 1 add the tile histograms of a catalog's sums workgroups
-// and scan them (count, start, cursor); workgroup 2 forms the catalog sums of both
-// (k_reduce_partials' order) and, with nm, the norms.
+// launch: workgroups 0, 1 add the tile histograms of a catalog's sums workgroups,
+// scan them (count, start) and leave in hist[b][t] where workgroup b's particles of
+// tile t go; workgroup 2 forms the catalog sums of both (k_reduce_partials' order)
+// and, with nm, the norms.
 __global__ void __launch_bounds__(1024) k_small_scan(SmallPair sp, int ntiles, int64_t ngal, double boxsize,
                                                      double* __restrict__ nm) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (blockIdx.x < 2) {
     const SmallCat c = sp.c[blockIdx.x];
     __shared__ uint32_t part[16][SMALL_TILES];
-    uint32_t v = 0;
-    if (lane < ntiles)
-      for (int b = wv; b < c.nblk; b += 16) v += c.hist[(int64_t)b * SMALL_TILES + lane];
+    constexpr int PB = SUMS_BLOCKS / 16;  // sums workgroups per wavefront: PB wv .. PB wv + PB - 1
+    uint32_t h[PB], v = 0;
+#pragma unroll
+    for (int k = 0; k < PB; ++k) {
+      const int b = PB * wv + k;
+      h[k] = b < c.nblk && lane < ntiles ? c.hist[(int64_t)b * SMALL_TILES + lane] : 0u;
+      v += h[k];
+    }
     part[wv][lane] = v;
     __syncthreads();
-    if (wv) return;
-    uint32_t cnt = 0;
-    for (int k = 0; k < 16; ++k) cnt += part[k][lane];
+    uint32_t cnt = 0, mine = 0;  // all wavefronts, the ones before this
+    for (int k = 0; k < 16; ++k) {
+      const uint32_t u = part[k][lane];
+      if (k < wv) mine += u;
+      cnt += u;
+    }
     uint32_t run = cnt;
     for (int off = 1; off < 64; off <<= 1) {
       const uint32_t u = __shfl_up(run, off, 64);
       if (lane >= off) run += u;
     }
-    if (lane < ntiles) {
+    if (lane >= ntiles) return;
+    if (wv == 0) {
       c.count[lane] = cnt;
       c.start[lane] = run - cnt;
-      c.cursor[lane] = run - cnt;
+    }
+    uint32_t base = run - cnt + mine;
+#pragma unroll
+    for (int k = 0; k < PB; ++k) {
+      const int b = PB * wv + k;
+      if (b < c.nblk) c.hist[(int64_t)b * SMALL_TILES + lane] = base;
+      base += h[k];
     }
     return;
   }
@@ -552,10 +571,12 @@ __host__ __device__ constexpr size_t partition_lds(int per, int rs, int rcap, in
 // rcap the chunk takes one global atomic per particle instead.
 // cursor[key] hands out output slots (initialised to the key's start).
 template <bool SOA, bool FINE, int RS, int PER, int NT>
-__device__ __forceinline__ void partition_block(const uint32_t* __restrict__ pos, const float* __restrict__ w,
-                                                const Rec<RS>* __restrict__ rin, int64_t n, const TileGeom& g,
-                                                int rcap, uint32_t* __restrict__ cursor, Rec<RS>* __restrict__ rout,
-                                                bool pack) {
+__global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ pos,
+                                                            const float* __restrict__ w,
+                                                            const Rec<RS>* __restrict__ rin,
+                                                            int64_t n, TileGeom g, int rcap,
+                                                            uint32_t* __restrict__ cursor,
+                                                            Rec<RS>* __restrict__ rout, bool pack) {
   constexpr int CH = NT * PER;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   Rec<RS>* stage = reinterpret_cast<Rec<RS>*>(smem_raw);                        // [CH]
@@ -630,23 +651,75 @@ __device__ __forceinline__ void partition_block(const uint32_t* __restrict__ pos
   }
 }
 
-template <bool SOA, bool FINE, int RS, int PER, int NT>
-__global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ pos,
-                                                            const float* __restrict__ w,
-                                                            const Rec<RS>* __restrict__ rin,
-                                                            int64_t n, TileGeom g, int rcap,
-                                                            uint32_t* __restrict__ cursor,
-                                                            Rec<RS>* __restrict__ rout, bool pack) {
-  partition_block<SOA, FINE, RS, PER, NT>(pos, w, rin, n, g, rcap, cursor, rout, pack);
-}
-
-// the one sort step of a mesh of one tile bucket, both catalogs in one launch
+// The one sort step of a mesh of one tile bucket, both catalogs in one launch:
+// workgroup b sorts the particles of sums workgroup b, whose place in every tile
+// k_small_scan has left in hist[b], chunk by chunk (a cursor per tile in LDS; one
+// atomic per chunk and tile on 64 shared counters took 25 us for 2.2e6 particles,
+// 15 us here).
 template <int RS, int PER>
 __global__ void __launch_bounds__(1024) k_partition2(SmallPair sp, TileGeom g, int ntiles) {
+  constexpr int NT = 1024, CH = NT * PER;
   const SmallCat c = sp.c[blockIdx.y];
-  if ((int64_t)blockIdx.x * 1024 * PER >= c.n) return;
-  partition_block<true, true, RS, PER, 1024>(c.pos, c.w, nullptr, c.n, g, ntiles, c.cursor,
-                                             reinterpret_cast<Rec<RS>*>(c.rec), false);
+  if ((int)blockIdx.x >= c.nblk) return;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  Rec<RS>* stage = reinterpret_cast<Rec<RS>*>(smem_raw);                        // [CH]
+  uint16_t* skey = reinterpret_cast<uint16_t*>(smem_raw + (size_t)CH * RS * 4);  // [CH]
+  __shared__ uint32_t hist[SMALL_TILES], lstart[SMALL_TILES], gbase[SMALL_TILES];
+  Rec<RS>* rout = reinterpret_cast<Rec<RS>*>(c.rec);
+  const int64_t r0 = sums_range(c.n, c.nblk) * blockIdx.x, r1 = min(c.n, r0 + sums_range(c.n, c.nblk));
+  if (threadIdx.x < SMALL_TILES) {
+    gbase[threadIdx.x] = (int)threadIdx.x < ntiles ? c.hist[(int64_t)blockIdx.x * SMALL_TILES + threadIdx.x] : 0u;
+    hist[threadIdx.x] = 0u;
+  }
+  __syncthreads();
+  for (int64_t c0 = r0; c0 < r1; c0 += CH) {
+    Rec<RS> r[PER];
+    int key[PER];
+    uint32_t rank[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {  // clamped straight-line loads, all in flight at once
+      const int64_t i = min(c0 + (int64_t)k * NT + threadIdx.x, r1 - 1);
+      r[k].v[0] = c.pos[i];
+      r[k].v[1] = c.pos[c.n + i];
+      r[k].v[2] = c.pos[2 * c.n + i];
+      if constexpr (RS == 4) r[k].v[3] = __float_as_uint(c.w[i]);
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      key[k] = c0 + (int64_t)k * NT + threadIdx.x < r1 ? tile_key(r[k].v[0], r[k].v[1], r[k].v[2], g) : -1;
+      if (key[k] >= 0) rank[k] = atomicAdd(&hist[key[k]], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {  // exclusive scan of the chunk's histogram
+      const uint32_t h = hist[threadIdx.x];
+      uint32_t run = h;
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t u = __shfl_up(run, off, 64);
+        if ((int)threadIdx.x >= off) run += u;
+      }
+      lstart[threadIdx.x] = run - h;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (key[k] >= 0) {
+        const uint32_t slot = lstart[key[k]] + rank[k];
+        stage[slot] = r[k];
+        skey[slot] = (uint16_t)key[k];
+      }
+    __syncthreads();
+    const int cnt = (int)min((int64_t)CH, r1 - c0);
+    for (int j = threadIdx.x; j < cnt; j += NT) {
+      const int kk = skey[j];
+      rout[gbase[kk] + (j - lstart[kk])] = stage[j];
+    }
+    __syncthreads();
+    if (threadIdx.x < SMALL_TILES) {
+      gbase[threadIdx.x] += hist[threadIdx.x];
+      hist[threadIdx.x] = 0u;
+    }
+    __syncthreads();
+  }
 }
 
 // ------------------------------------------------------ fused bucket pass --
@@ -1772,9 +1845,8 @@ PaintLayout paint_layout(const cnpc_mesh_desc* d, int64_t ngal, int64_t nran, bo
   L.off_count[1] = off; off = align_up(off + (size_t)L.ntiles * 4);
   L.off_partial = off; off = align_up(off + (size_t)BUCKET_BLOCKS_MAX * CNPC_SUMS_LEN * 8);
   L.off_sums = off; off = align_up(off + (size_t)2 * CNPC_SUMS_LEN * 8);
-  const size_t slots = L.nbuckets == 1 ? 2 * SMALL_TILES : (size_t)L.ntiles;
-  L.off_start = off; off = align_up(off + slots * 4);
-  L.off_cursor = off; off = align_up(off + slots * 4);
+  L.off_start = off; off = align_up(off + (L.nbuckets == 1 ? 2 * SMALL_TILES : (size_t)L.ntiles) * 4);
+  L.off_cursor = off; off = align_up(off + (size_t)L.ntiles * 4);
   L.off_hist = off; off = align_up(off + (L.nbuckets == 1 ? (size_t)2 * SUMS_BLOCKS * SMALL_TILES * 4 : 0));
   L.off_bcur = off; off = align_up(off + (size_t)L.nbuckets * 4);
   for (int k = 0; k < L.nsets; ++k) {
@@ -1919,7 +1991,6 @@ static cnpc_status paint_small(const cnpc_mesh_desc* d, const uint32_t* const* p
     k.hist = reinterpret_cast<uint32_t*>(ws + L.off_hist) + (size_t)c * SUMS_BLOCKS * SMALL_TILES;
     k.count = reinterpret_cast<uint32_t*>(ws + L.off_count[c]);
     k.start = reinterpret_cast<uint32_t*>(ws + L.off_start) + c * SMALL_TILES;
-    k.cursor = reinterpret_cast<uint32_t*>(ws + L.off_cursor) + c * SMALL_TILES;
     k.rec = ws + L.off_rec + c * rec;
     k.sums = sums[c];
     pc.rec[c] = reinterpret_cast<const Rec<RS>*>(k.rec);
@@ -1942,13 +2013,11 @@ static cnpc_status paint_small(const cnpc_mesh_desc* d, const uint32_t* const* p
   CNPC_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_small_scan, dim3(3), dim3(1024), 0, s, sp, L.ntiles, n[0], d->boxsize, norms);
   CNPC_HIP(hipGetLastError());
-  // chunks of 4 particles per thread once they fill the CUs, of 1 below that
-  const int per = nmax >= (int64_t)1024 * 4 * 256 ? 4 : 1;
-  const unsigned pblk = (unsigned)((nmax + 1024 * per - 1) / (1024 * per));
-  const size_t lds = partition_lds(per, RS, L.ntiles, 1024);
+  // chunks of 4 particles per thread for ranges of more than one chunk of 1
+  const int per = sums_range(nmax, sums_blocks(nmax)) > 1024 ? 4 : 1;
   kt_begin(CNPC_KT_SORT, s);
-  hipLaunchKernelGGL((per == 4 ? k_partition2<RS, 4> : k_partition2<RS, 1>), dim3(pblk, 2), dim3(1024), lds, s, sp, g,
-                     L.ntiles);
+  hipLaunchKernelGGL((per == 4 ? k_partition2<RS, 4> : k_partition2<RS, 1>), dim3((unsigned)nblk, 2), dim3(1024),
+                     (size_t)1024 * per * (RS * 4 + 2), s, sp, g, L.ntiles);
   kt_end(CNPC_KT_SORT, s);
   CNPC_HIP(hipGetLastError());
   return launch_paint_tiles<T, RS>(d, weighted, 2, pc, L, s);
