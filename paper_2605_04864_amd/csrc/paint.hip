@@ -1927,15 +1927,16 @@ static cnpc_status launch_partition(const uint32_t* pos, const float* w, const R
   return CNPC_OK;
 }
 
-// Tile painting of tile-sorted records: ncat catalogs in one launch
+// Tile painting of tile-sorted records: ncat catalogs in one launch, the w^2 blocks
+// with `second`
 template <typename T, int RS>
-static cnpc_status launch_paint_tiles(const cnpc_mesh_desc* d, bool weighted, int ncat, const PaintCats<T, RS>& pc,
+static cnpc_status launch_paint_tiles(const cnpc_mesh_desc* d, bool second, int ncat, const PaintCats<T, RS>& pc,
                                       const PaintLayout& L, hipStream_t s) {
   const TileGeom g = tile_geom(d);
   kt_begin(CNPC_KT_PAINT, s);
   if constexpr (sizeof(T) == 4 && RS == 3) {
     // unit weights: w^2 = w, the second power's blocks are painted alike
-    for (int pw = 0; pw < (weighted ? 2 : 1); ++pw) {
+    for (int pw = 0; pw < (second ? 2 : 1); ++pw) {
       PaintCats<T, RS> p = pc;
       for (int c = 0; c < ncat; ++c) p.blocks[c] = pc.blocks[c + 2 * pw];
       hipLaunchKernelGGL((d->assign == CNPC_TSC ? k_paint_tiles_u32<CNPC_TSC> : k_paint_tiles_u32<CNPC_CIC>),
@@ -1943,7 +1944,7 @@ static cnpc_status launch_paint_tiles(const cnpc_mesh_desc* d, bool weighted, in
                          packs_records(true, 3, g.shift));
     }
   } else {
-    const int npow = weighted ? 2 : 1;
+    const int npow = second ? 2 : 1;
     hipLaunchKernelGGL((d->assign == CNPC_TSC ? k_paint_tiles<T, CNPC_TSC, RS> : k_paint_tiles<T, CNPC_CIC, RS>),
                        dim3((unsigned)(L.ntiles * L.nphase * npow), (unsigned)ncat), dim3(1024), 0, s, pc, g, L.nphase,
                        npow);
@@ -1955,15 +1956,15 @@ static cnpc_status launch_paint_tiles(const cnpc_mesh_desc* d, bool weighted, in
 
 // the records of set set0 (rec, start of the layout, its count)
 template <typename T, int RS>
-static cnpc_status paint_sorted(const cnpc_mesh_desc* d, bool weighted, int set0, unsigned char* ws,
+static cnpc_status paint_sorted(const cnpc_mesh_desc* d, bool second, int set0, unsigned char* ws,
                                 const PaintLayout& L, hipStream_t s) {
   PaintCats<T, RS> pc{};
   pc.rec[0] = reinterpret_cast<const Rec<RS>*>(ws + L.off_rec);
   pc.start[0] = reinterpret_cast<const uint32_t*>(ws + L.off_start);
   pc.count[0] = reinterpret_cast<const uint32_t*>(ws + L.off_count[set0]);
   pc.blocks[0] = reinterpret_cast<T*>(ws + L.off_blocks[set0]);
-  if (weighted) pc.blocks[2] = reinterpret_cast<T*>(ws + L.off_blocks[set0 + 2]);
-  return launch_paint_tiles<T, RS>(d, weighted, 1, pc, L, s);
+  if (second) pc.blocks[2] = reinterpret_cast<T*>(ws + L.off_blocks[set0 + 2]);
+  return launch_paint_tiles<T, RS>(d, second, 1, pc, L, s);
 }
 
 // Meshes of one tile bucket (N <= 64), both catalogs with weights or both
@@ -1973,7 +1974,7 @@ static cnpc_status paint_sorted(const cnpc_mesh_desc* d, bool weighted, int set0
 // 171 us with 31 launches before, 146 with 21; P_0,2,4 on 64^3 225 before, 193.
 template <typename T, int RS>
 static cnpc_status paint_small(const cnpc_mesh_desc* d, const uint32_t* const* pos, const float* const* w,
-                               const int64_t* n, bool weighted, int lmax, double* const* sums, double* norms,
+                               const int64_t* n, bool second, int lmax, double* const* sums, double* norms,
                                unsigned char* ws, const PaintLayout& L, hipStream_t s) {
   const TileGeom g = tile_geom(d);
   SmallPair sp;
@@ -1997,7 +1998,7 @@ static cnpc_status paint_small(const cnpc_mesh_desc* d, const uint32_t* const* p
     pc.start[c] = k.start;
     pc.count[c] = k.count;
     pc.blocks[c] = reinterpret_cast<T*>(ws + L.off_blocks[c]);
-    if (weighted) pc.blocks[c + 2] = reinterpret_cast<T*>(ws + L.off_blocks[c + 2]);
+    if (second) pc.blocks[c + 2] = reinterpret_cast<T*>(ws + L.off_blocks[c + 2]);
     nblk = std::max(nblk, k.nblk);
     nmax = std::max(nmax, n[c]);
   }
@@ -2020,12 +2021,12 @@ static cnpc_status paint_small(const cnpc_mesh_desc* d, const uint32_t* const* p
                      (size_t)1024 * per * (RS * 4 + 2), s, sp, g, L.ntiles);
   kt_end(CNPC_KT_SORT, s);
   CNPC_HIP(hipGetLastError());
-  return launch_paint_tiles<T, RS>(d, weighted, 2, pc, L, s);
+  return launch_paint_tiles<T, RS>(d, second, 2, pc, L, s);
 }
 
 template <typename T, int RS>
 static cnpc_status sort_and_paint(const cnpc_mesh_desc* d, const uint32_t* pos, const float* w, int64_t n,
-                                  int set0, bool weighted, bool counted, unsigned char* ws,
+                                  int set0, bool second, bool counted, unsigned char* ws,
                                   const PaintLayout& L, hipStream_t s) {
   const TileGeom g = tile_geom(d);
   uint32_t* count = reinterpret_cast<uint32_t*>(ws + L.off_count[set0]);
@@ -2056,7 +2057,7 @@ static cnpc_status sort_and_paint(const cnpc_mesh_desc* d, const uint32_t* pos, 
   } else {
     CNPC_TRY((launch_partition<true, true, RS>(pos, w, nullptr, n, g, L.ntiles, cursor, rec, pack, s)));
   }
-  return paint_sorted<T, RS>(d, weighted, set0, ws, L, s);
+  return paint_sorted<T, RS>(d, second, set0, ws, L, s);
 }
 
 // Catalog sums, tile histogram and both sort steps from one read of the
@@ -2105,7 +2106,7 @@ static void launch_bucket_pass(const BucketShape& b, unsigned nblk, size_t lds, 
 
 template <typename T, int RS>
 static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t* pos, const float* w, int64_t n,
-                                        int set0, bool weighted, int sums_lmax, double* sums, unsigned char* ws,
+                                        int set0, bool second, int sums_lmax, double* sums, unsigned char* ws,
                                         const PaintLayout& L, hipStream_t s) {
   const TileGeom g = tile_geom(d);
   uint32_t* count = reinterpret_cast<uint32_t*>(ws + L.off_count[set0]);
@@ -2210,7 +2211,7 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
                          bcnt, bcnt + L.nbuckets, cap, cpb, L.nbuckets, g, cursor, out64);
     kt_end(CNPC_KT_SORT, s);
     CNPC_HIP(hipGetLastError());
-    return paint_sorted<T, RS>(d, weighted, set0, ws, L, s);
+    return paint_sorted<T, RS>(d, second, set0, ws, L, s);
   }
   if (tper == 4)
     hipLaunchKernelGGL((k_tile_pass<RS, 4, 1024>), dim3(tgrid), dim3(1024), tlds, s, region, ovf_rec, bcnt,
@@ -2223,7 +2224,7 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
                        bcnt + L.nbuckets, cap, cpb, L.nbuckets, g, cursor, rec, pack);
   kt_end(CNPC_KT_SORT, s);
   CNPC_HIP(hipGetLastError());
-  return paint_sorted<T, RS>(d, weighted, set0, ws, L, s);
+  return paint_sorted<T, RS>(d, second, set0, ws, L, s);
 }
 
 // the one-bucket route of paint_small: both catalogs weighted or both not
@@ -2240,7 +2241,9 @@ static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const 
                            const double* norms, T* delta, T* noise, unsigned char* ws,
                            const PaintLayout& L, bool counted, hipStream_t s, int sums_lmax = -1,
                            double* gs = nullptr, double* rs = nullptr, bool fold = true, bool form_norms = true) {
-  const bool weighted = (gw != nullptr) || (rw != nullptr);
+  // the w^2 blocks are painted and folded only where an N mesh (or the fused fold)
+  // takes them; without weights they are the w blocks
+  const bool weighted = (gw != nullptr) || (rw != nullptr), second = weighted && (noise != nullptr || !fold);
   const uint32_t* cpos[2] = {gpos, rpos};
   const float* cw[2] = {gw, rw};
   const int64_t cn[2] = {ngal, nran};
@@ -2248,27 +2251,27 @@ static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const 
   fa.n = d->n;
   fa.nt = L.nt;
   fa.nphase = L.nphase;
-  fa.nsets = L.nsets;
+  fa.nsets = second ? 4 : 2;
   const bool small = sums_lmax >= 0 && paint_is_small(L, gw, rw);
   if (small) {
     double* sums_c[2] = {gs, rs};
     double* nm = form_norms ? const_cast<double*>(norms) : nullptr;
-    if (weighted) CNPC_TRY((paint_small<T, 4>(d, cpos, cw, cn, true, sums_lmax, sums_c, nm, ws, L, s)));
+    if (weighted) CNPC_TRY((paint_small<T, 4>(d, cpos, cw, cn, second, sums_lmax, sums_c, nm, ws, L, s)));
     else CNPC_TRY((paint_small<T, 3>(d, cpos, cw, cn, false, sums_lmax, sums_c, nm, ws, L, s)));
   }
   for (int c = 0; c < 2; ++c) {
-    for (int pw = 0; pw < (weighted ? 2 : 1); ++pw)
+    for (int pw = 0; pw < (second ? 2 : 1); ++pw)
       fa.blocks[c + 2 * pw] = reinterpret_cast<T*>(ws + L.off_blocks[c + 2 * pw]);
     if (small) continue;
     double* sums_c = c == 0 ? gs : rs;
     if (sums_lmax >= 0 && cw[c])
-      CNPC_TRY((fused_sort_and_paint<T, 4>(d, cpos[c], cw[c], cn[c], c, weighted, sums_lmax, sums_c, ws, L, s)));
+      CNPC_TRY((fused_sort_and_paint<T, 4>(d, cpos[c], cw[c], cn[c], c, second, sums_lmax, sums_c, ws, L, s)));
     else if (sums_lmax >= 0)
-      CNPC_TRY((fused_sort_and_paint<T, 3>(d, cpos[c], nullptr, cn[c], c, weighted, sums_lmax, sums_c, ws, L, s)));
+      CNPC_TRY((fused_sort_and_paint<T, 3>(d, cpos[c], nullptr, cn[c], c, second, sums_lmax, sums_c, ws, L, s)));
     else if (cw[c])
-      CNPC_TRY((sort_and_paint<T, 4>(d, cpos[c], cw[c], cn[c], c, weighted, counted, ws, L, s)));
+      CNPC_TRY((sort_and_paint<T, 4>(d, cpos[c], cw[c], cn[c], c, second, counted, ws, L, s)));
     else
-      CNPC_TRY((sort_and_paint<T, 3>(d, cpos[c], nullptr, cn[c], c, weighted, counted, ws, L, s)));
+      CNPC_TRY((sort_and_paint<T, 3>(d, cpos[c], nullptr, cn[c], c, second, counted, ws, L, s)));
   }
   if (sums_lmax >= 0 && form_norms && !small) CNPC_TRY(launch_norms(d, gs, rs, ngal, const_cast<double*>(norms), s));
   if (!fold) return CNPC_OK;
