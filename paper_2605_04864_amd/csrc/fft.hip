@@ -783,7 +783,7 @@ static cnpc_status zr2c_n(const T* in, cx<T>* out, int64_t nrows, int kz, hipStr
 template <typename T, int N>
 static cnpc_status zc2r_n(const cx<T>* in, T* out, int64_t nrows, int kz, hipStream_t s) {
   const int64_t npairs = nrows / 2;
-  if constexpr (N == 512) if (fft_register_passes()) {
+  if constexpr (N == 512 || (N == 128 && sizeof(T) == 8)) if (fft_register_passes()) {
     constexpr int GR = 2048 / N;
     const size_t lds = sizeof(cx<T>) * (N + (size_t)GR * group_lds<N>);
     kt_begin(CNPC_KT_ZC2R, s);
@@ -794,7 +794,7 @@ static cnpc_status zc2r_n(const cx<T>* in, T* out, int64_t nrows, int kz, hipStr
     return CNPC_OK;
   }
   constexpr int R1 = q_radix(N);
-  if constexpr (R1 > 0 && N != 512) if (fft_register_passes()) {
+  if constexpr (N == 128 && sizeof(T) == 4) if (fft_register_passes()) {
     constexpr int R2 = 2 * R1, GR = 256 / R1;
     const size_t lds = sizeof(cx<T>) * (N + (size_t)GR * R2 * (R1 + 1));
     kt_begin(CNPC_KT_ZC2R, s);
