@@ -90,18 +90,21 @@ static double q_factor_host(int l1, int l2, int L, double k1, double k2, double 
 //   l even: F0 Re y (part 0), -F0 Im y (part 1)
 //   l odd:  -i F0 Im y (part 0), -i F0 Re y (part 1)
 // each Hermitian, so that a c2r gives the real field.
+// F0 has half-width m, out the half-width mo <= m of the shells' band: weighting all of
+// the band and copying its middle took 15.5 us a leg (FP64, band 64, shells to 32),
+// this 4.9; the double arithmetic of y bounds it.
 template <typename T>
-__global__ void __launch_bounds__(256) k_weight_ylm(int m, int ell, int em, int part,
+__global__ void __launch_bounds__(256) k_weight_ylm(int m, int mo, int ell, int em, int part,
                                                     const cx<T>* __restrict__ F0, cx<T>* __restrict__ out) {
-  const int64_t bsz = (int64_t)4 * m * m * m;
+  const int64_t total = (int64_t)4 * mo * mo * mo;
   const int am = em < 0 ? -em : em;
   const double sg = (em < 0 && (am & 1)) ? -1.0 : 1.0;  // y^-m = (-1)^m conj(y^m)
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < bsz;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * blockDim.x) {
-    const int kz = (int)(i % m);
-    const int jy = (int)((i / m) % (2 * m));
-    const int jx = (int)(i / ((int64_t)2 * m * m));
-    const int nx = band_freq(jx, m), ny = band_freq(jy, m), nz = kz;
+    const int kz = (int)(i % mo);
+    const int jy = (int)((i / mo) % (2 * mo));
+    const int jx = (int)(i / ((int64_t)2 * mo * mo));
+    const int nx = band_freq(jx, mo), ny = band_freq(jy, mo), nz = kz;
     const int64_t n2 = (int64_t)nx * nx + (int64_t)ny * ny + (int64_t)nz * nz;
     double wgt = 0.0;
     if (n2 > 0) {
@@ -111,7 +114,8 @@ __global__ void __launch_bounds__(256) k_weight_ylm(int m, int ell, int em, int 
       const double re = sg * yr[am], im = (em < 0 ? -sg : sg) * yi[am];
       wgt = (ell & 1) ? (part == 0 ? im : re) : (part == 0 ? re : -im);
     }
-    const cx<T> f = F0[i];
+    const int sx = nx < 0 ? nx + 2 * m : nx, sy = ny < 0 ? ny + 2 * m : ny;
+    const cx<T> f = F0[((int64_t)sx * 2 * m + sy) * m + kz];
     if (ell & 1)  // times -i
       out[i] = cx<T>{T(wgt * (double)f.y), T(-wgt * (double)f.x)};
     else
@@ -120,10 +124,15 @@ __global__ void __launch_bounds__(256) k_weight_ylm(int m, int ell, int em, int 
 }
 
 // out = scale * in / W(q) on the band of an n^3 mesh; zero at q = 0 and on
-// modes with a Nyquist component
+// modes with a Nyquist component; the windows from a table of their sines in LDS
+// (band 64: 14.8 us a call with them per mode, 9.3 so)
 template <typename T>
 __global__ void __launch_bounds__(256) k_div_window(int n, int m, int assign, double scale,
                                                     const cx<T>* __restrict__ in, cx<T>* __restrict__ out) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* win = reinterpret_cast<double*>(smem_raw);  // [2m] window of band index j
+  for (int j = threadIdx.x; j < 2 * m; j += 256) win[j] = window_1d(band_freq(j, m), n, assign);
+  __syncthreads();
   const int64_t bsz = (int64_t)4 * m * m * m;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < bsz;
        i += (int64_t)gridDim.x * blockDim.x) {
@@ -136,7 +145,7 @@ __global__ void __launch_bounds__(256) k_div_window(int n, int m, int assign, do
       out[i] = cx<T>{T(0), T(0)};
       continue;
     }
-    const double W = window_1d(nx, n, assign) * window_1d(ny, n, assign) * window_1d(nz, n, assign);
+    const double W = win[jx] * win[jy] * win[kz];
     const cx<T> a = in[i];
     out[i] = cx<T>{T(scale * (double)a.x / W), T(scale * (double)a.y / W)};
   }
@@ -419,14 +428,19 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
   // leg field (l, m, part) of every shell into a slot, from F_0 (signal) or
   // from ones (harmonic shell indicators of the FFT-method noise)
   const cx<T>* legsrc = F0;
+  const int ms = shell_band(P->thr.data(), nb, m);
   auto load_leg = [&](T* slot, int ell, int em, int part) -> cnpc_status {
-    hipLaunchKernelGGL((k_weight_ylm<T>), dim3(gb), dim3(256), 0, s, m, ell, em, part, legsrc, spec);
+    // weighted in the band of the shells (an eighth of the modes at half the band)
+    const int64_t sub = (int64_t)4 * ms * ms * ms;
+    hipLaunchKernelGGL((k_weight_ylm<T>), dim3((unsigned)std::min<int64_t>((sub + 255) / 256, 65536)), dim3(256), 0, s,
+                       m, ms, ell, em, part, legsrc, spec);
     CNPC_HIP(hipGetLastError());
-    return shell_c2r<T>(&dg, m, spec, P->thr.data(), nb + 1, 0, nb, true, slot, scr, s);
+    return shell_c2r<T>(&dg, ms, spec, P->thr.data(), nb + 1, 0, nb, true, slot, scr, s);
   };
   // one unmasked band c2r of scale * in / W into a slot
   auto load_los = [&](T* slot, const cx<T>* in, double scale) -> cnpc_status {
-    hipLaunchKernelGGL((k_div_window<T>), dim3(gb), dim3(256), 0, s, P->desc.n, m, P->desc.assign, scale, in, spec);
+    hipLaunchKernelGGL((k_div_window<T>), dim3(std::min(gb, 1024u)), dim3(256), sizeof(double) * 2 * m, s, P->desc.n,
+                       m, P->desc.assign, scale, in, spec);
     CNPC_HIP(hipGetLastError());
     return shell_c2r<T>(&dg, m, spec, P->thr.data(), nb + 1, 0, 1, false, slot, scr, s);
   };
