@@ -650,16 +650,26 @@ __global__ void __launch_bounds__(256) k_xpass_interlace_rr(const cx<T>* __restr
   for (int k2 = 0; k2 < R; ++k2) out[(int64_t)(rank + R * k2) * ROW + col] = va[k2];
 }
 
-// k_xpass_interlace_rr for N = 128, 512 in column groups (8 values per lane of
-// each phase).  It replaces both forward x passes, the combination pass and the
+// The value of i in a register that the compiler takes as new: what is computed from it
+// (LDS addresses of an exchange) isn't kept over from an earlier use.
+__device__ __forceinline__ int opaque(int i) {
+  asm volatile("" : "+v"(i));
+  return i;
+}
+
+// k_xpass_interlace_rr for N = 128, 512 and FP64 256 in column groups (8 values per
+// lane of each phase).  It replaces both forward x passes, the combination pass and the
 // inverse x pass: two spectra read and one written in place of five and four.
-// 512^3: FP32 two x passes, combination and inverse 770 us before, 521 us here;
-// FP64 1870 us before, 1257 us here (5.1 TB/s).
-template <typename T, int N>
-__global__ void __launch_bounds__(N / 8 * col_g_width<T>)
+// 512^3: FP32 two x passes, combination and inverse 770 us before, 514 us here;
+// FP64 1870 us before, 1244 us here (2.6 TB/s: one workgroup of 173 registers a lane
+// fits per CU, so loads and transforms don't overlap; held to 128 registers, two
+// workgroups, it spills and takes 1193).  FP64 256^3: 124 us with 302 registers a lane
+// in k_xpass_interlace_rr, 93 us here (4.3 TB/s).
+template <typename T, int N, int W>
+__global__ void __launch_bounds__(N / 8 * W, sizeof(T) == 8 ? 2 : 4)
     k_xpass_interlace_g(const cx<T>* __restrict__ in, cx<T>* __restrict__ out, cx<T>* __restrict__ band_out, int mb,
                         T scale) {
-  constexpr int W = col_g_width<T>, L = N / 8, H = N / 2;
+  constexpr int L = N / 8, H = N / 2;
   constexpr int64_t ROW = (int64_t)N * H, PHASE = (int64_t)N * N * H;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   // [2N]: exp(-i pi s / N), the interlacing phase of nx + ny + kz = s (mod 2N);
@@ -672,16 +682,17 @@ __global__ void __launch_bounds__(N / 8 * col_g_width<T>)
   }
   const int c = threadIdx.x % W, t = threadIdx.x / W;
   const int col = blockIdx.x * W + c;
+  // one 32-bit offset per lane; the rows' steps are uniform
+  const uint32_t o = (uint32_t)t * (uint32_t)ROW + (uint32_t)col;
   cx<T> va[8], vb[8];
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
-    const int64_t o = (int64_t)(t + L * r) * ROW + col;
-    va[r] = in[o];
-    vb[r] = in[PHASE + o];
+    va[r] = (in + L * r * ROW)[o];
+    vb[r] = (in + PHASE + L * r * ROW)[o];
   }
   __syncthreads();  // twiddles
-  col_fft_g<T, N, W, -1, 2>(va, c, t, buf, tph);
-  col_fft_g<T, N, W, -1, 2>(vb, c, t, buf, tph);
+  col_fft_g<T, N, W, -1, 2>(va, opaque(c), opaque(t), buf, tph);
+  col_fft_g<T, N, W, -1, 2>(vb, opaque(c), opaque(t), buf, tph);
   const int iy = col / H, kz = col - iy * H;
   const int ny = iy < H ? iy : iy - N;
 #pragma unroll
@@ -696,20 +707,20 @@ __global__ void __launch_bounds__(N / 8 * col_g_width<T>)
     }
     va[i] = cscale(d, scale);
   }
-  col_fft_g<T, N, W, 1, 2, true>(va, c, t, buf, tph);
+  col_fft_g<T, N, W, 1, 2, true>(va, opaque(c), opaque(t), buf, tph);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) out[(int64_t)(t + L * i) * ROW + col] = va[i];
+  for (int i = 0; i < 8; ++i) (out + L * i * ROW)[o] = va[i];
 }
 
 template <typename T>
 cnpc_status xpass_interlace(int n, const cx<T>* in, cx<T>* out, cx<T>* band_out, int mb, T scale,
                             hipStream_t s) {
   auto gog = [&](auto nc) -> cnpc_status {
-    constexpr int N = decltype(nc)::value, W = col_g_width<T>;
+    constexpr int N = decltype(nc)::value, W = sizeof(T) == 8 ? 8 : 16;
     const int64_t cols = (int64_t)N * (N / 2);
     const size_t lds = sizeof(cx<T>) * (2 * N + (size_t)N * W);
     kt_begin(CNPC_KT_COL, s);
-    hipLaunchKernelGGL((k_xpass_interlace_g<T, N>), dim3((unsigned)(cols / W)), dim3(N / 8 * W), lds, s, in, out,
+    hipLaunchKernelGGL((k_xpass_interlace_g<T, N, W>), dim3((unsigned)(cols / W)), dim3(N / 8 * W), lds, s, in, out,
                        band_out, mb, scale);
     kt_end(CNPC_KT_COL, s);
     CNPC_HIP(hipGetLastError());
@@ -717,6 +728,7 @@ cnpc_status xpass_interlace(int n, const cx<T>* in, cx<T>* out, cx<T>* band_out,
   };
   if (n == 128) return gog(std::integral_constant<int, 128>());
   if (n == 512) return gog(std::integral_constant<int, 512>());
+  if constexpr (sizeof(T) == 8) if (n == 256) return gog(std::integral_constant<int, 256>());
   auto go = [&](auto rc) -> cnpc_status {
     constexpr int R = decltype(rc)::value, N = R * R, W = 256 / R;
     const int64_t cols = (int64_t)N * (N / 2);
@@ -729,7 +741,7 @@ cnpc_status xpass_interlace(int n, const cx<T>* in, cx<T>* out, cx<T>* band_out,
     return CNPC_OK;
   };
   if (n == 64) return go(std::integral_constant<int, 8>());
-  if (n == 256) return go(std::integral_constant<int, 16>());
+  if constexpr (sizeof(T) == 4) if (n == 256) return go(std::integral_constant<int, 16>());
   set_error("fused interlace pass needs N = 64 .. 512 (got %d)", n);
   return CNPC_EUNSUPPORTED;
 }

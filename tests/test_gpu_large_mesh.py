@@ -143,9 +143,9 @@ def test_paint_weights_beyond_the_mantissa_range(n, assign, dtype, tol):
             assert np.max(e) <= tol * np.max(np.abs(ref[ph]))
 
 
-@pytest.mark.parametrize("n,band,dtype", [(128, 64, L.F32), (128, 16, L.F64), (512, 64, L.F32), (512, 128, L.F64)])
+@pytest.mark.parametrize("n,band,dtype", [(128, 64, L.F32), (128, 16, L.F64), (256, 32, L.F64), (512, 64, L.F32), (512, 128, L.F64)])
 def test_deinterlace_fused_x_pass(n, band, dtype):
-    """The fused x pass of 128 and 512 (both phases forward, combination, band
+    """The fused x pass of 128, FP64 256 and 512 (both phases forward, combination, band
     copy, inverse) against the plain passes (CNPC_TUNE_FFT_PASSES 1)."""
     d = cn.mesh_desc(n, 1000.0, interlace=True, dtype=dtype)
     x = torch.randn((2, n, n, n), dtype=torch.float64, device="cuda",
