@@ -154,8 +154,8 @@ cnpc_status cnpc_paint(const cnpc_mesh_desc* desc, const uint32_t* gpos, const f
                        const double* norms, void* delta, void* noise, void* ws, size_t ws_bytes,
                        void* stream);
 /* cnpc_catalog_sums of both catalogs, cnpc_norms and cnpc_paint in one call:
- * the tile histogram of the sort is taken during the catalog-sum pass, which
- * saves one read of every particle.  sums_lmax (0, 2 or 4): the Y_l^m sums
+ * the l = 0 sums are taken while the particles are sorted, which saves a read
+ * of every particle.  sums_lmax (0, 2 or 4): the Y_l^m sums
  * (and Sbar_l^m) are formed for l <= sums_lmax only, the others are zero; the
  * l = 0 sums are always formed.  gal_sums, ran_sums: CNPC_SUMS_LEN device
  * doubles each, or NULL when not wanted; norms: CNPC_NORMS_LEN device doubles
