@@ -19,6 +19,32 @@ static Geo make_geo(const cnpc_mesh_desc* d) {
   return g;
 }
 
+// g with its lengths in units of the power of two below the largest of them.  The
+// passes by powers of R and r_z form R^4 and R^-4, which leave FP32 from R of
+// 4e9 on (and below 2e-10) in the caller's units; the harmonics do not depend on
+// the unit, and a power of two changes no mantissa.
+static Geo unit_geo(Geo g, int n) {
+  double len = g.h * n;
+  for (int i = 0; i < 3; ++i) len = fmax(len, fabs(g.obs[i]));
+  const int e = -ilogb(len);
+  g.h = ldexp(g.h, e);
+  for (int i = 0; i < 3; ++i) g.obs[i] = ldexp(g.obs[i], e);
+  return g;
+}
+
+// Whether those passes may take the mesh: they form r_z along a row by additions,
+// so the direction of a node next to the observer is lost in their rounding (and
+// R^-4 with it); within a quarter of a cell the fields are formed from directions.
+static bool ylm_powers_ok(const Geo& g, int n) {
+  if (g.global_los) return true;
+  double r2 = 0.0;
+  for (int i = 0; i < 3; ++i) {
+    const double u = g.obs[i] / g.h, du = u - fmin(fmax(nearbyint(u), 0.0), n - 1.0);
+    r2 += du * du;
+  }
+  return r2 >= 0.0625;
+}
+
 struct FieldTable {
   int nf;
   signed char ell[32], m[32], part[32];
@@ -988,11 +1014,14 @@ static cnpc_status zylm_n(const T* delta, cx<T>* out, const FieldTable& ft, int 
 
 // z pass of the Y_lm fields: by powers of r_z in lane groups for FP64 at 64 ..
 // 512 and FP32 at 128, 512 (FP32 at 64 and 256 has the register passes of
-// zylm_rr); CNPC_TUNE_YLM_BASIS 1 takes one transform per field everywhere
+// zylm_rr); CNPC_TUNE_YLM_BASIS 1 takes one transform per field everywhere, an
+// observer next to a node (ylm_powers_ok) the passes from directions
 template <typename T>
 static cnpc_status zpass_ylm(int n, const T* delta, cx<T>* out, const FieldTable& ft, int kz,
-                             int64_t fstride, const Geo& g, hipStream_t s) {
-  if (fft_register_passes() && tune_value(CNPC_TUNE_YLM_BASIS) != 1) {
+                             int64_t fstride, const Geo& g0, hipStream_t s) {
+  const bool powers = ylm_powers_ok(g0, n);
+  const Geo g = unit_geo(g0, n);
+  if (powers && fft_register_passes() && tune_value(CNPC_TUNE_YLM_BASIS) != 1) {
     if (n == 128) return zylm_g<T, 128>(delta, out, ft, kz, fstride, g, s);
     if (n == 512) return zylm_g<T, 512>(delta, out, ft, kz, fstride, g, s);
     if constexpr (sizeof(T) == 8) {
@@ -1001,17 +1030,19 @@ static cnpc_status zpass_ylm(int n, const T* delta, cx<T>* out, const FieldTable
     }
   }
   switch (n) {
-    case 16: return zylm_rr<T, 4>(delta, out, ft, kz, fstride, g, s);
-    case 32: return zylm_n<T, 32>(delta, out, ft, kz, fstride, g, s);
+    case 16:
+      if (powers) return zylm_rr<T, 4>(delta, out, ft, kz, fstride, g, s);
+      return zylm_n<T, 16>(delta, out, ft, kz, fstride, g0, s);
+    case 32: return zylm_n<T, 32>(delta, out, ft, kz, fstride, g0, s);
     case 64:
-      if (fft_register_passes()) return zylm_rr<T, 8>(delta, out, ft, kz, fstride, g, s);
-      return zylm_n<T, 64>(delta, out, ft, kz, fstride, g, s);
-    case 128: return zylm_n<T, 128>(delta, out, ft, kz, fstride, g, s);
+      if (powers && fft_register_passes()) return zylm_rr<T, 8>(delta, out, ft, kz, fstride, g, s);
+      return zylm_n<T, 64>(delta, out, ft, kz, fstride, g0, s);
+    case 128: return zylm_n<T, 128>(delta, out, ft, kz, fstride, g0, s);
     case 256:
-      if (fft_register_passes()) return zylm_rr<T, 16>(delta, out, ft, kz, fstride, g, s);
-      return zylm_n<T, 256>(delta, out, ft, kz, fstride, g, s);
-    case 512: return zylm_n<T, 512>(delta, out, ft, kz, fstride, g, s);
-    case 1024: return zylm_n<T, 1024>(delta, out, ft, kz, fstride, g, s);
+      if (powers && fft_register_passes()) return zylm_rr<T, 16>(delta, out, ft, kz, fstride, g, s);
+      return zylm_n<T, 256>(delta, out, ft, kz, fstride, g0, s);
+    case 512: return zylm_n<T, 512>(delta, out, ft, kz, fstride, g0, s);
+    case 1024: return zylm_n<T, 1024>(delta, out, ft, kz, fstride, g0, s);
     default: set_error("unsupported mesh size %d", n); return CNPC_EUNSUPPORTED;
   }
 }
@@ -1037,7 +1068,8 @@ template cnpc_status band_forward_yx<double>(int, int, int, int, const cx<double
 // CNPC_TUNE_YLM_BASIS 0: the z pass writes the z-power bases, the y pass forms
 // the fields from them (coefficient table next to the bases in w1)
 template <typename T>
-static bool ylm_bases_route(int n, int m, const FieldTable& ft, const YlmBases& yb) {
+static bool ylm_bases_route(int n, int m, const FieldTable& ft, const YlmBases& yb, const Geo& g) {
+  if (!ylm_powers_ok(g, n)) return false;
   if (sizeof(T) != 4 || n != 256 || m % 16 != 0 || !fft_register_passes()) return false;
   if (tune_value(CNPC_TUNE_YLM_BASIS) == 1) return false;
   const size_t nn = (size_t)n * n;
@@ -1053,11 +1085,12 @@ static cnpc_status ylm_r2c_t(const cnpc_mesh_desc* d, int band, const FieldTable
   const int64_t nn = (int64_t)n * n;
   cx<T>* w1 = ws;
   cx<T>* w2 = ws + (int64_t)ft.nf * nn * m;
-  const Geo g = make_geo(d);
-  const YlmBases yb = ylm_bases(ft, g.global_los != 0);
+  const Geo g0 = make_geo(d);
+  const YlmBases yb = ylm_bases(ft, g0.global_los != 0);
   if constexpr (sizeof(T) == 4) {
-    if (ylm_bases_route<T>(n, m, ft, yb)) {
+    if (ylm_bases_route<T>(n, m, ft, yb, g0)) {
       constexpr int R = 16, N = 256, GR = 256 / R;
+      const Geo g = unit_geo(g0, n);
       const T* coef = coef_in;
       kt_begin(CNPC_KT_ZR2C, s);
       if (!coef) {
@@ -1090,7 +1123,7 @@ static cnpc_status ylm_r2c_t(const cnpc_mesh_desc* d, int band, const FieldTable
     set_error("Y_lm transform of z spectra: only the FP32 z-power-bases route takes them");
     return CNPC_EUNSUPPORTED;
   }
-  CNPC_TRY(zpass_ylm<T>(n, delta, w1, ft, m, nn * m, g, s));
+  CNPC_TRY(zpass_ylm<T>(n, delta, w1, ft, m, nn * m, g0, s));
   return band_forward_yx<T>(n, d->dtype, ft.nf, m, w1, w2, out, s);
 }
 
@@ -1120,7 +1153,7 @@ size_t ylm_coef_bytes(const cnpc_mesh_desc* d, int nells, const int32_t* ells, i
   FieldTable ft;
   if (d->dtype != CNPC_F32 || field_table(nells, ells, &ft) <= 0) return 0;
   const YlmBases yb = ylm_bases(ft, d->los_mode == CNPC_LOS_GLOBAL);
-  if (!ylm_bases_route<float>(d->n, band, ft, yb)) return 0;
+  if (!ylm_bases_route<float>(d->n, band, ft, yb, make_geo(d))) return 0;
   return (size_t)ft.nf * d->n * d->n * 4 * sizeof(float);
 }
 
@@ -1129,7 +1162,7 @@ cnpc_status launch_ylm_coef(const cnpc_mesh_desc* d, int nells, const int32_t* e
   FieldTable ft;
   CNPC_REQUIRE(field_table(nells, ells, &ft) > 0, "too many Y_lm fields (max 32)");
   CNPC_REQUIRE(ylm_coef_bytes(d, nells, ells, band) > 0, "no coefficient table for this transform");
-  const Geo g = make_geo(d);
+  const Geo g = unit_geo(make_geo(d), d->n);
   const YlmBases yb = ylm_bases(ft, g.global_los != 0);
   const int64_t ncoef = (int64_t)ft.nf * d->n * d->n;
   hipLaunchKernelGGL((k_ylm_coef<float>), dim3((unsigned)((ncoef + 255) / 256)), dim3(256), 0, s, ft, yb, d->n, g,
