@@ -421,8 +421,8 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_tile_count(const uint32_t* __res
 // Exclusive scan of R values by a workgroup of NT threads: emit(r, sum_{q < r}
 // in[q]) for every r, each thread handling a run of consecutive r.  Wave
 // prefix sums plus one LDS slot per wave (wsum, NT / 64 entries).
-template <int NT, typename Emit>
-__device__ void block_exclusive_scan(const uint32_t* in, int R, uint32_t* wsum, Emit emit) {
+template <int NT, typename U, typename Emit>
+__device__ void block_exclusive_scan(const U* in, int R, uint32_t* wsum, Emit emit) {
   const int per = (R + NT - 1) / NT;
   const int t0 = threadIdx.x * per, t1 = min(R, t0 + per);
   uint32_t s = 0;
@@ -900,16 +900,130 @@ __global__ void __launch_bounds__(NT) k_bucket_pass(const uint32_t* __restrict__
     }
 }
 
+// Overflow records lie in runs of one bucket, one per (workgroup, chunk, bucket)
+// of the bucket pass, so a chunk of them holds few buckets.  The passes over them
+// number the buckets of a chunk (the first OVF_SLOTS in key order; the rest take
+// global atomics) and count and sort in LDS by (bucket number, tile in bucket),
+// as the region chunks do.  A catalog that fills a part of its box has most of its
+// records here: with one global atomic per record 2.2e7 particles in 1 / 64 of a
+// 256^3 box took 34 ms (FP64 P_0 pass) before, 2.9 here, in 1 / 8 of it 6.1 ms
+// before, 1.8 here.
+constexpr int OVF_SLOTS = 32;
+
+// flag, slot: [nbuckets]; list: [nslots].  Numbers the buckets tk[k] >> bshift
+// (tk[k] >= 0) of a chunk: slot[b] (255 past the first nslots), list[slot] = b.
+// Starts and ends with a workgroup barrier.
+template <int NT, int PER>
+__device__ __forceinline__ void number_buckets(const int* tk, int bshift, int nbuckets, int nslots, uint8_t* flag,
+                                               uint8_t* slot, uint32_t* list, uint32_t* wsum) {
+  __syncthreads();
+  for (int b = threadIdx.x; b < nbuckets; b += NT) flag[b] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PER; ++k)
+    if (tk[k] >= 0) flag[tk[k] >> bshift] = 1;
+  __syncthreads();
+  block_exclusive_scan<NT>(flag, nbuckets, wsum, [&](int b, uint32_t v) {
+    if (!flag[b]) return;
+    slot[b] = (uint8_t)(v < (uint32_t)nslots ? v : 255u);
+    if (v < (uint32_t)nslots) list[v] = b;
+  });
+  __syncthreads();
+}
+
+// records per thread of an overflow chunk of a tile pass with per ones (the tables
+// leave two workgroups per CU whole chunks of 8-byte records, half chunks of others)
+__host__ __device__ constexpr int ovf_per(int per, int vbytes) { return per > 1 && vbytes > 8 ? per / 2 : per; }
+// LDS bytes of sort_overflow
+__host__ __device__ constexpr size_t overflow_lds(int per, int vbytes, int nt, int nbuckets, int bshift) {
+  return (size_t)nt * per * (vbytes + 2) + (size_t)4 * (3 * (OVF_SLOTS << bshift) + OVF_SLOTS + 16) + 2 * (size_t)nbuckets;
+}
+
+// Tile step over the overflow records c0 .. (one workgroup's share): load(c, i, v)
+// reads record c + i and returns its tile, put(o, v) writes one to output slot o.
+template <int NT, int PER, typename V, typename Load, typename Put>
+__device__ __forceinline__ void sort_overflow(int64_t c0, int64_t stride, uint32_t no, int nbuckets, int bshift,
+                                              uint32_t* __restrict__ cursor, unsigned char* smem, Load load, Put put) {
+  constexpr int CH = NT * PER;
+  const int R = OVF_SLOTS << bshift, mask = (1 << bshift) - 1;
+  V* stage = reinterpret_cast<V*>(smem);                                          // [CH]
+  uint16_t* skey = reinterpret_cast<uint16_t*>(smem + (size_t)CH * sizeof(V));     // [CH]
+  uint32_t* hist = reinterpret_cast<uint32_t*>(smem + (size_t)CH * (sizeof(V) + 2));  // [R] each
+  uint32_t *lstart = hist + R, *gbase = lstart + R;
+  uint32_t* list = gbase + R;       // [OVF_SLOTS]
+  uint32_t* wsum = list + OVF_SLOTS;  // 16 slots
+  uint8_t *flag = reinterpret_cast<uint8_t*>(wsum + 16), *slot = flag + nbuckets;
+  if (c0 >= no) return;
+  V rn[PER];  // the next chunk, loaded while the current one is sorted (clamped indices)
+  int tn[PER];
+  auto load_chunk = [&](int64_t c) {
+    const int last = (int)min((int64_t)CH, no - c) - 1;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) tn[k] = load(c, (uint32_t)min(k * NT + (int)threadIdx.x, last), rn[k]);
+  };
+  load_chunk(c0);
+  for (; c0 < no; c0 += stride) {
+    V r[PER];
+    int tk[PER];  // tile, then (bucket number, tile in bucket) | rank << 16; < 0: none
+    const int cin = (int)min((int64_t)CH, no - c0);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      r[k] = rn[k];
+      tk[k] = k * NT + (int)threadIdx.x < cin ? tn[k] : -1;
+    }
+    if (c0 + stride < no) load_chunk(c0 + stride);
+    number_buckets<NT, PER>(tk, bshift, nbuckets, OVF_SLOTS, flag, slot, list, wsum);
+    for (int t = threadIdx.x; t < R; t += NT) hist[t] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      if (tk[k] < 0) continue;
+      const int b = slot[tk[k] >> bshift];
+      if (b < OVF_SLOTS) {
+        tk[k] = (b << bshift) | (tk[k] & mask);
+        tk[k] |= (int)(atomicAdd(&hist[tk[k]], 1u) << 16);
+      } else {
+        put(atomicAdd(&cursor[tk[k]], 1u), r[k]);
+        tk[k] = -1;
+      }
+    }
+    __syncthreads();
+    block_exclusive_scan<NT>(hist, R, wsum, [&](int t, uint32_t v) {
+      lstart[t] = v;
+      const uint32_t c = hist[t];
+      gbase[t] = c ? atomicAdd(&cursor[(list[t >> bshift] << bshift) | (t & mask)], c) : 0u;
+    });
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (tk[k] >= 0) {
+        const uint32_t j = lstart[tk[k] & 0xffff] + (uint32_t)(tk[k] >> 16);
+        stage[j] = r[k];
+        skey[j] = (uint16_t)tk[k];
+      }
+    __syncthreads();
+    const int cnt = (int)(lstart[R - 1] + hist[R - 1]);
+    for (int j = threadIdx.x; j < cnt; j += NT) {
+      const int kk = skey[j];
+      put(gbase[kk] + (j - lstart[kk]), stage[j]);
+    }
+  }
+}
+
 // Tile histogram of bucket-sorted records, for meshes of more tiles than the
 // bucket pass holds in LDS (512^3 and more).  A bucket's records fall into its
 // own S^3 <= 64 tiles, so a workgroup counts REGION_CHUNK of them in LDS (one
-// copy per wavefront) and adds each tile once; only the overflow records take
-// an atomic each.  Bound by its reads: the 16-bit tile indices of packed
+// copy per wavefront) and adds each tile once; the overflow records are counted
+// by the buckets of a chunk.  Bound by its reads: the 16-bit tile indices of packed
 // records (2 bytes a particle) or the records themselves (12 or 16).  One
 // global atomic per particle in the bucket pass, which it replaces, held that
 // pass to 2.6 ms for 5.5e7 particles (0.90 ms without it, and 0.04 ms here; 3.3e8
 // full records: 0.80 ms here).
 constexpr int REGION_CHUNK = 65536;
+constexpr int COUNT_PER = 8, COUNT_SLOTS = 64;  // overflow chunks: records per thread, buckets
+__host__ __device__ constexpr size_t region_count_lds(int nbuckets, int bshift) {
+  return (size_t)4 * ((COUNT_SLOTS << bshift) + COUNT_SLOTS + 16) + 2 * (size_t)nbuckets;
+}
 template <int RS>
 __global__ void __launch_bounds__(1024) k_region_count(const Rec<RS>* __restrict__ region,
                                                        const uint16_t* __restrict__ rkey,
@@ -922,12 +1036,37 @@ __global__ void __launch_bounds__(1024) k_region_count(const Rec<RS>* __restrict
   __shared__ uint32_t hist[16][64];
   const int nreg = nbuckets * chunks_per_bucket;
   if ((int)blockIdx.x >= nreg) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int bshift = 3 * g.ls, R = COUNT_SLOTS << bshift, mask = (1 << bshift) - 1;
+    uint32_t* oh = reinterpret_cast<uint32_t*>(smem_raw);  // [R]
+    uint32_t *list = oh + R, *wsum = list + COUNT_SLOTS;
+    uint8_t *flag = reinterpret_cast<uint8_t*>(wsum + 16), *slot = flag + nbuckets;
     const uint32_t no = *ovf;
-    for (uint32_t i = (blockIdx.x - nreg) * 1024u + threadIdx.x; i < no; i += (gridDim.x - nreg) * 1024u) {
-      int t;
-      if (packed) t = okey[i];
-      else t = tile_key(ovf_in[i].v[0], ovf_in[i].v[1], ovf_in[i].v[2], g);
-      atomicAdd(&count[t], 1u);
+    constexpr int64_t CH = 1024 * COUNT_PER;
+    for (int64_t c0 = (int64_t)(blockIdx.x - nreg) * CH; c0 < no; c0 += (int64_t)(gridDim.x - nreg) * CH) {
+      int tk[COUNT_PER];
+#pragma unroll
+      for (int k = 0; k < COUNT_PER; ++k) {
+        const int64_t i = c0 + k * 1024 + (int)threadIdx.x, ii = min(i, (int64_t)no - 1);
+        if (packed) tk[k] = okey[ii];
+        else tk[k] = tile_key(ovf_in[ii].v[0], ovf_in[ii].v[1], ovf_in[ii].v[2], g);
+        if (i >= no) tk[k] = -1;
+      }
+      number_buckets<1024, COUNT_PER>(tk, bshift, nbuckets, COUNT_SLOTS, flag, slot, list, wsum);
+      for (int t = threadIdx.x; t < R; t += 1024) oh[t] = 0u;
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < COUNT_PER; ++k) {
+        if (tk[k] < 0) continue;
+        const int b = slot[tk[k] >> bshift];
+        if (b < COUNT_SLOTS) atomicAdd(&oh[(b << bshift) | (tk[k] & mask)], 1u);
+        else atomicAdd(&count[tk[k]], 1u);
+      }
+      __syncthreads();
+      for (int t = threadIdx.x; t < R; t += 1024) {
+        const uint32_t c = oh[t];
+        if (c) atomicAdd(&count[(list[t >> bshift] << bshift) | (t & mask)], c);
+      }
     }
     return;
   }
@@ -966,10 +1105,10 @@ __global__ void __launch_bounds__(1024) k_region_count(const Rec<RS>* __restrict
 
 // Second counting-sort step over the bucket regions: workgroup (b, j) sorts
 // records j CH .. of bucket b (its keys lie in bucket b); workgroups past the
-// last region chunk walk the overflow records (mixed buckets: one global slot
-// per particle).
+// last region chunk sort the overflow records (sort_overflow, chunks of half
+// the size: its tables take the other half of the LDS).
 template <int RS, int PER, int NT>
-__global__ void __launch_bounds__(NT) k_tile_pass(const Rec<RS>* __restrict__ region,
+__global__ void __launch_bounds__(NT, 8) k_tile_pass(const Rec<RS>* __restrict__ region,
                                                   const Rec<RS>* __restrict__ ovf_in, const uint32_t* __restrict__ bcnt,
                                                   const uint32_t* __restrict__ ovf, uint32_t cap, int chunks_per_bucket,
                                                   int nbuckets, TileGeom g, uint32_t* __restrict__ cursor,
@@ -980,17 +1119,15 @@ __global__ void __launch_bounds__(NT) k_tile_pass(const Rec<RS>* __restrict__ re
   const int R = 1 << bshift;  // tiles per bucket
   const int nreg = nbuckets * chunks_per_bucket;
   if ((int)blockIdx.x >= nreg) {
-    const uint32_t no = *ovf;
-    for (int64_t c0 = (int64_t)(blockIdx.x - nreg) * CH; c0 < no; c0 += (int64_t)(gridDim.x - nreg) * CH) {
-#pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        const int64_t i = c0 + (int64_t)k * NT + threadIdx.x;
-        if (i < no) {
-          const Rec<RS> rr = ovf_in[i];
-          put_rec(rout, atomicAdd(&cursor[tile_key(rr.v[0], rr.v[1], rr.v[2], g)], 1u), rr, pack, g.shift);
-        }
-      }
-    }
+    constexpr int OP = ovf_per(PER, RS * 4);
+    sort_overflow<NT, OP, Rec<RS>>(
+        (int64_t)(blockIdx.x - nreg) * NT * OP, (int64_t)(gridDim.x - nreg) * NT * OP, *ovf, nbuckets, bshift, cursor,
+        smem_raw,
+        [&](int64_t c, uint32_t i, Rec<RS>& v) {
+          v = (ovf_in + c)[i];
+          return tile_key(v.v[0], v.v[1], v.v[2], g);
+        },
+        [&](uint32_t o, const Rec<RS>& v) { put_rec(rout, o, v, pack, g.shift); });
     return;
   }
   const int b = blockIdx.x / chunks_per_bucket, jc = blockIdx.x - b * chunks_per_bucket;
@@ -1045,7 +1182,7 @@ __global__ void __launch_bounds__(NT) k_tile_pass(const Rec<RS>* __restrict__ re
 // index, for the FP32 painter): the tile index comes from its own array and the
 // packed records are moved as they are
 template <int PER, int NT>
-__global__ void __launch_bounds__(NT) k_tile_pass_packed(const uint64_t* __restrict__ region,
+__global__ void __launch_bounds__(NT, 8) k_tile_pass_packed(const uint64_t* __restrict__ region,
                                                          const uint16_t* __restrict__ rkey,
                                                          const uint64_t* __restrict__ ovf_in,
                                                          const uint16_t* __restrict__ okey,
@@ -1059,14 +1196,15 @@ __global__ void __launch_bounds__(NT) k_tile_pass_packed(const uint64_t* __restr
   const int R = 1 << bshift;
   const int nreg = nbuckets * chunks_per_bucket;
   if ((int)blockIdx.x >= nreg) {
-    const uint32_t no = *ovf;
-    for (int64_t c0 = (int64_t)(blockIdx.x - nreg) * CH; c0 < no; c0 += (int64_t)(gridDim.x - nreg) * CH) {
-#pragma unroll
-      for (int k = 0; k < PER; ++k) {
-        const int64_t i = c0 + (int64_t)k * NT + threadIdx.x;
-        if (i < no) rout[atomicAdd(&cursor[okey[i]], 1u)] = ovf_in[i];
-      }
-    }
+    constexpr int OP = ovf_per(PER, 8);
+    sort_overflow<NT, OP, uint64_t>(
+        (int64_t)(blockIdx.x - nreg) * NT * OP, (int64_t)(gridDim.x - nreg) * NT * OP, *ovf, nbuckets, bshift, cursor,
+        smem_raw,
+        [&](int64_t c, uint32_t i, uint64_t& v) {
+          v = (ovf_in + c)[i];
+          return (int)(okey + c)[i];
+        },
+        [&](uint32_t o, uint64_t v) { rout[o] = v; });
     return;
   }
   const int b = blockIdx.x / chunks_per_bucket, jc = blockIdx.x - b * chunks_per_bucket;
@@ -1819,7 +1957,7 @@ static TileGeom tile_geom(const cnpc_mesh_desc* d) {
 // mean bucket count plus the largest chunk (more goes to the overflow region).
 constexpr int BUCKET_NT = 1024;
 constexpr int BUCKET_BLOCKS_MAX = 512;
-constexpr int OVF_BLOCKS = 256;  // tile-pass workgroups walking the overflow records
+constexpr int OVF_BLOCKS = 512;  // tile-pass workgroups walking the overflow records (two per CU)
 static uint32_t bucket_cap(int64_t n, int nbuckets) {
   const int64_t mean = (n + nbuckets - 1) / nbuckets;
   const int64_t c = mean + mean / 2 + (int64_t)BUCKET_NT * 8;
@@ -2168,7 +2306,8 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   if (ltiles == 0) {
     const int rcpb = (int)((cap + REGION_CHUNK - 1) / REGION_CHUNK);
     kt_begin(CNPC_KT_SORT, s);
-    hipLaunchKernelGGL((k_region_count<RS>), dim3((unsigned)(L.nbuckets * rcpb + OVF_BLOCKS)), dim3(1024), 0, s, region,
+    hipLaunchKernelGGL((k_region_count<RS>), dim3((unsigned)(L.nbuckets * rcpb + OVF_BLOCKS)), dim3(1024),
+                       region_count_lds(L.nbuckets, 3 * g.ls), s, region,
                        ba.rkey, ovf_rec, ba.okey, bcnt, bcnt + L.nbuckets, cap, rcpb, L.nbuckets, g, packb, count);
     kt_end(CNPC_KT_SORT, s);
     CNPC_HIP(hipGetLastError());
@@ -2195,10 +2334,12 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   const int64_t tch = (int64_t)1024 * tper;
   const int cpb = (int)((cap + tch - 1) / tch);
   const unsigned tgrid = (unsigned)(L.nbuckets * cpb + OVF_BLOCKS);
-  const size_t tlds = partition_lds(tper, RS, per_bucket, 1024);
+  const size_t tlds = std::max(partition_lds(tper, RS, per_bucket, 1024),
+                               overflow_lds(ovf_per(tper, RS * 4), RS * 4, 1024, L.nbuckets, 3 * g.ls));
   kt_begin(CNPC_KT_SORT, s);
   if (packb) {
-    const size_t plds = (size_t)1024 * tper * 10 + (size_t)3 * per_bucket * 4 + 64;
+    const size_t plds = std::max((size_t)1024 * tper * 10 + (size_t)3 * per_bucket * 4 + 64,
+                                 overflow_lds(ovf_per(tper, 8), 8, 1024, L.nbuckets, 3 * g.ls));
     const uint64_t* r64 = reinterpret_cast<const uint64_t*>(region);
     const uint64_t* o64 = reinterpret_cast<const uint64_t*>(ovf_rec);
     uint64_t* out64 = reinterpret_cast<uint64_t*>(rec);
