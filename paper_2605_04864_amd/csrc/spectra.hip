@@ -1437,20 +1437,35 @@ cnpc_status launch_assemble(const cnpc_mesh_desc* d, int band, int ell, const vo
 }
 
 // ---------------------------------------------------------------- binning --
-// A thread takes `run` consecutive kz of a row (nx, ny), along which |n|^2 grows
-// (8 from band 128 up, 4 at 64, 2 below, where longer runs would leave CUs idle), and adds its shell sums to LDS when the bin changes: a shell holds several
-// neighbouring kz, whose atomics would meet on one address.  Windows and alias
-// sums come from tables over the band index.  NP: accumulators per thread
-// (npairs + nself <= NP).  Band 64, 2 pairs and a self term, FP64: 56 us with
-// an atomic per mode and FP64 trigonometry per mode before, 37 here; band 128 302 before,
-// 254 here.
-static int bin_run(int m) { return std::min(m, m >= 128 ? 8 : m == 64 ? 4 : 2); }
-template <typename T, int NP>
-__global__ void __launch_bounds__(256) k_bin(BinArgs<T> a, int run, const double* __restrict__ norms,
+// A thread takes `run` consecutive modes along ny (or kz), along which |n|^2 is
+// monotone, and adds its shell sums to LDS when the bin changes: neighbouring modes
+// of a shell would meet on one LDS address (an atomic per mode).  With runs along ny
+// the lanes are neighbouring kz and every load is a run of whole lines; runs along kz,
+// a lane `run` modes from the next, go through more lines than the L1 holds from three
+// spectra on, but read each once for all of a run's modes, which the two wavefronts per
+// SIMD of the kernel with self terms (their harmonics take 100 registers) are too few to
+// hide: those with one FP64 or two FP32 pairs, from band 128 up, run along kz.  NP: accumulators per thread
+// (npairs + nself <= NP), four pairs loaded at a time.  FP64, 20 bins, us: one atomic per
+// mode / runs along kz alone / here:
+//   band 128: 1 pair 127 / 95 / 78, 4 pairs 212 / 263 / 112, 9 pairs 290 / 539 / 158,
+//   4 pairs and a self term 292 / 288 / 193; band 256: 1 pair 984 / 607 / 511, 9 pairs
+//   2323 / 3146 / 1064.
+struct BinRun {
+  int len;      // modes per thread, a power of two: 4 from band 64 up (8 along kz), fewer
+                // below, where longer runs would leave CUs idle
+  bool along_z;
+  int blocks;   // workgroups at most: each sets up its tables and adds all bins to memory
+};
+static BinRun bin_run(int m, int npairs, int nself, size_t es) {
+  if (m >= 128 && nself && npairs * es <= 8) return {8, true, 2048};
+  return {m >= 64 ? 4 : m == 32 ? 2 : 1, false, m >= 128 ? 2048 : 512};
+}
+template <typename T, int NP, bool SELF>
+__global__ void __launch_bounds__(256) k_bin(BinArgs<T> a, int run, bool along_z, const double* __restrict__ norms,
                                              double* __restrict__ acc_out,
                                              unsigned long long* __restrict__ cnt_out) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int nq = a.npairs + a.nself, nacc = nq + 1;  // + sum |k|
+  const int nq = a.npairs + (SELF ? a.nself : 0), nacc = nq + 1;  // + sum |k|
   const int m = a.m, n = a.n;
   double* acc = reinterpret_cast<double*>(smem_raw);
   unsigned long long* cnt = reinterpret_cast<unsigned long long*>(acc + (int64_t)a.nbins * nacc);
@@ -1458,24 +1473,29 @@ __global__ void __launch_bounds__(256) k_bin(BinArgs<T> a, int run, const double
   double *al = win + 2 * m, *at = al + 2 * m;
   for (int i = threadIdx.x; i < a.nbins * nacc; i += blockDim.x) acc[i] = 0.0;
   for (int i = threadIdx.x; i < a.nbins; i += blockDim.x) cnt[i] = 0ull;
-  if (a.nself)
+  if constexpr (SELF)
     for (int j = threadIdx.x; j < 2 * m; j += blockDim.x) {
       win[j] = window_1d(band_freq(j, m), n, a.assign);
       alias_1d(band_freq(j, m), n, a.assign, &al[j], &at[j]);
     }
   __syncthreads();
-  const int per = m / run;
-  const int64_t nruns = (int64_t)4 * m * m * per;
+  const int lm = 31 - __clz(m), lrun = 31 - __clz(run);  // m and run are powers of two
+  const int64_t nruns = (int64_t)1 << (3 * lm + 2 - lrun);
+  const int sz = along_z ? 1 : 0, sy = 1 - sz;  // steps of a run
   for (int64_t ir = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; ir < nruns;
        ir += (int64_t)gridDim.x * blockDim.x) {
-    const int kz0 = (int)(ir % per) * run;
-    const int64_t row = ir / per;
-    const int jy = (int)(row % (2 * m)), jx = (int)(row / (2 * m));
-    const int nx = band_freq(jx, m), ny = band_freq(jy, m);
-    if (nx == -(n / 2) || ny == -(n / 2)) continue;
-    const int64_t nxy = (int64_t)nx * nx + (int64_t)ny * ny;
-    const int kz1 = kz0 + run - 1;
-    if (nxy + (int64_t)kz1 * kz1 < a.thr[0] || nxy + (int64_t)kz0 * kz0 >= a.thr[a.nbins]) continue;
+    // run index: (jx, jy, kz run) or (jx, jy run, kz)
+    const int lz = along_z ? lm - lrun : lm, ly = along_z ? lm + 1 : lm + 1 - lrun;
+    const int kz0 = ((int)ir & ((1 << lz) - 1)) << (lm - lz);
+    const int jy0 = ((int)(ir >> lz) & ((1 << ly) - 1)) << (lm + 1 - ly);
+    const int jx = (int)(ir >> (lz + ly));
+    const int nx = band_freq(jx, m), ny0 = band_freq(jy0, m);
+    if (nx == -(n / 2)) continue;
+    const int64_t nx2 = (int64_t)nx * nx;
+    const int ny1 = ny0 + sy * (run - 1), kz1 = kz0 + sz * (run - 1);
+    const int64_t y0 = (int64_t)ny0 * ny0, y1 = (int64_t)ny1 * ny1;
+    if (nx2 + max(y0, y1) + (int64_t)kz1 * kz1 < a.thr[0] || nx2 + min(y0, y1) + (int64_t)kz0 * kz0 >= a.thr[a.nbins])
+      continue;
     double v[NP], vk = 0.0;
 #pragma unroll
     for (int q = 0; q < NP; ++q) v[q] = 0.0;
@@ -1496,10 +1516,10 @@ __global__ void __launch_bounds__(256) k_bin(BinArgs<T> a, int run, const double
       vk = 0.0;
       c = 0;
     };
-    for (int kz = kz0; kz <= kz1; ++kz) {
-      const int64_t n2 = nxy + (int64_t)kz * kz;
-      if (kz == n / 2 || n2 == 0 || n2 < a.thr[0]) continue;
-      if (n2 >= a.thr[a.nbins]) break;
+    for (int j = 0; j < run; ++j) {
+      const int ny = ny0 + sy * j, kz = kz0 + sz * j, jy = jy0 + sy * j;
+      const int64_t n2 = nx2 + (int64_t)ny * ny + (int64_t)kz * kz;
+      if (ny == -(n / 2) || n2 == 0 || n2 < a.thr[0] || n2 >= a.thr[a.nbins]) continue;
       if (bin < 0) {
         int lo = 0, hi = a.nbins;
         while (hi - lo > 1) {
@@ -1507,26 +1527,27 @@ __global__ void __launch_bounds__(256) k_bin(BinArgs<T> a, int run, const double
           if (n2 >= a.thr[mid]) lo = mid; else hi = mid;
         }
         bin = lo;
-      } else if (n2 >= a.thr[bin + 1]) {
+      } else if (n2 >= a.thr[bin + 1] || n2 < a.thr[bin]) {
         flush();
-        do ++bin; while (n2 >= a.thr[bin + 1]);
+        while (n2 >= a.thr[bin + 1]) ++bin;
+        while (n2 < a.thr[bin]) --bin;
       }
-      const int64_t i = row * m + kz;
+      const int64_t i = ((((int64_t)jx << (lm + 1)) + jy) << lm) + kz;
       const double wgt = kz == 0 ? 1.0 : 2.0;
+      // four pairs at a time, all loads before the first use; the first ones are on
+      // their way while the self terms are formed
+      cx<T> fa[4], fb[4];
+      auto load = [&](int q0) {
 #pragma unroll
-      for (int q = 0; q < NP; ++q) {
-        if (q < a.npairs) {
-          const cx<T> fa = a.pa[q][i], fb = a.pb[q][i];
-          // Re or Im of F_a F_b^*; for an anti-Hermitian product (odd l) the
-          // k and -k halves carry the same imaginary part, so the half-grid
-          // weights apply to both
-          const double f = ((a.imag >> q) & 1u) ? (double)fa.y * (double)fb.x - (double)fa.x * (double)fb.y
-                                                : (double)fa.x * (double)fb.x + (double)fa.y * (double)fb.y;
-          v[q] += wgt * f;
+        for (int q = 0; q < 4; ++q) {
+          if (q0 + q >= a.npairs) break;
+          fa[q] = a.pa[q0 + q][i];
+          fb[q] = a.pb[q0 + q][i];
         }
-      }
+      };
+      load(0);
       const double kn = sqrt((double)n2);
-      if (a.nself) {
+      if constexpr (SELF) {
         const double ux = nx / kn, uy = ny / kn, uz = kz / kn;
         const double C = a.interlace ? 0.5 * (al[jx] * al[jy] * al[kz] + at[jx] * at[jy] * at[kz])
                                      : al[jx] * al[jy] * al[kz];
@@ -1543,6 +1564,22 @@ __global__ void __launch_bounds__(256) k_bin(BinArgs<T> a, int run, const double
 #pragma unroll
           for (int e = 0; e < NP; ++e)
             if (e == a.npairs + q) v[e] += wgt * f * cw;
+        }
+      }
+#pragma unroll
+      for (int q0 = 0; q0 < MAX_PAIRS && q0 < NP; q0 += 4) {
+        if (q0 < a.npairs) {
+          if (q0) load(q0);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (q0 + q >= a.npairs) break;
+            // Re or Im of F_a F_b^*; for an anti-Hermitian product (odd l) the
+            // k and -k halves carry the same imaginary part, so the half-grid
+            // weights apply to both
+            const double f = ((a.imag >> (q0 + q)) & 1u) ? (double)fa[q].y * (double)fb[q].x - (double)fa[q].x * (double)fb[q].y
+                                                         : (double)fa[q].x * (double)fb[q].x + (double)fa[q].y * (double)fb[q].y;
+            v[q0 + q] += wgt * f;
+          }
         }
       }
       vk += wgt * kn;
@@ -1615,15 +1652,21 @@ static cnpc_status bin_t(const cnpc_mesh_desc* d, const int64_t* thr, int nbins,
   const int64_t nacc_tot = (int64_t)nbins * nacc;
   hipLaunchKernelGGL(k_bin_zero, dim3(1), dim3(256), 0, s, acc, nacc_tot, nmodes, (int64_t)nbins);
   CNPC_HIP(hipGetLastError());
-  const int run = bin_run(band);
-  const int64_t nruns = (int64_t)4 * band * band * (band / run);
-  const unsigned g = (unsigned)std::min<int64_t>((nruns + 255) / 256, 2048);
+  const BinRun run = bin_run(band, npairs, nself, sizeof(T));
+  const int64_t nruns = (int64_t)4 * band * band * band / run.len;
+  const unsigned g = (unsigned)std::min<int64_t>((nruns + 255) / 256, run.blocks);
   const size_t lds = sizeof(double) * nacc_tot + sizeof(unsigned long long) * nbins +
                      (nself ? sizeof(double) * 6 * band : 0);
   const int nq = npairs + nself;
   kt_begin(CNPC_KT_BIN, s);
-  hipLaunchKernelGGL((nq <= 4 ? k_bin<T, 4> : nq <= 8 ? k_bin<T, 8> : k_bin<T, MAX_PAIRS + MAX_SELF>), dim3(g), dim3(256),
-                     lds, s, a, run, norms, acc, (unsigned long long*)nmodes);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(g), dim3(256), lds, s, a, run.len, run.along_z, norms, acc,
+                       (unsigned long long*)nmodes);
+  };
+  if (nself)
+    go(nq <= 4 ? k_bin<T, 4, true> : nq <= 8 ? k_bin<T, 8, true> : nq <= 12 ? k_bin<T, 12, true>
+                                                                  : k_bin<T, MAX_PAIRS + MAX_SELF, true>);
+  else go(nq <= 4 ? k_bin<T, 4, false> : nq <= 8 ? k_bin<T, 8, false> : k_bin<T, MAX_PAIRS, false>);
   kt_end(CNPC_KT_BIN, s);
   CNPC_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_bin_finish, dim3(1), dim3(256), 0, s, acc, nmodes, nbins, npairs, nself,
