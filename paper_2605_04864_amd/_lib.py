@@ -159,10 +159,13 @@ def ptr(t) -> int | None:
 
 def stream_handle(stream=None) -> int:
     if stream is None:
-        # the raw handle: torch.cuda.current_stream() builds a Stream object per call, a
-        # tenth of the host time of a small measurement
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # torch.cuda.current_stream() builds a Stream object per call, a tenth of the
+        # host time of a small measurement; the raw handle is torch's own, not public
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 
