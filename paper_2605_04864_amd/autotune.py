@@ -11,9 +11,9 @@ The setting is
   contract_kg  point groups per split-BF16 contraction workgroup (0: library's)
   sort_per     particles per thread of the sort scatter (0: library's)
   sort_threads threads per sort-scatter workgroup (0: library's)
-  sort_fused   how the catalog sums and the first sort step share reads (0, 1, 2)
+  sort_fused   sort through bucket regions (0) or after a histogram pass (1)
   fold_fused   fold inside the de-interlacing z passes (0) or meshes written (1)
-  bucket       shape of the first sort step (0, 1, 2)
+  bucket       shape of the first sort step (0, 1, 2, 3)
 
 All but the stream count are the library's tuning knobs (``cnpc_tune_set``); the search
 is one coordinate-descent sweep in that order, each value timed with the
@@ -73,6 +73,15 @@ def coordinate_descent(space: Dict[str, Sequence], start: Dict, measure: Callabl
             if t < best_t * (1.0 - min_gain):
                 best, best_t = cand, t
     return best, best_t, trials
+
+
+def search_space(streams: Sequence[int]) -> Dict[str, List[int]]:
+    """Values the tuner times: those of every knob that differ from each other
+    (sort_fused 2 is sort_fused 0; five column widths)."""
+    space = {"streams": list(streams), **{k: list(L.TUNE[k][1]) for k in KNOB_ORDER}}
+    space["sort_fused"] = [0, 1]
+    space["fft_col_w"] = [0, 4, 8, 16, 32]
+    return space
 
 
 def signature(desc, plan, ncat: int, ells: Sequence[int]) -> str:
@@ -186,9 +195,7 @@ def tune_batch(desc, catalogs, bins, plan, ells=(0, 2, 4), streams: Sequence[int
             set_knobs(hit["knobs"])
             return TuneResult(int(hit["streams"]), dict(hit["knobs"]), float(hit["ms"]), float(hit["default_ms"]),
                               0.0, True, [])
-    space = {"streams": list(streams)}
-    for k in KNOB_ORDER:
-        space[k] = list(L.TUNE[k][1]) if k != "fft_col_w" else [0, 4, 8, 16, 32]
+    space = search_space(streams)
     s0 = DEFAULT_STREAMS if DEFAULT_STREAMS in streams else streams[0]
     start = {"streams": s0, **{k: 0 for k in KNOB_ORDER}}
 
