@@ -276,12 +276,16 @@ __global__ void k_sugi_finalize(SugiFin f, const double* __restrict__ acc, const
 }
 
 // ------------------------------------------------------------------ plan --
+// grid fields of a run: P, Q_a, Q_b of every shell and two line-of-sight fields; the
+// FP32 contractions take W of every shell and an all-ones field besides
+static int sugi_slots(int nb, size_t es) { return es == 8 ? 3 * nb + 2 : 4 * nb + 3; }
+
 static size_t sugi_ws_bytes(const cnpc_mesh_desc* d, const cnpc_kbins* b) {
   const BispecGeom g = bispec_geometry(d, b, CNPC_EST_TRIPOSH, 0);
   const int nb = b->nbins, m = g.band;
   const size_t g3 = (size_t)g.grid * g.grid * g.grid, es = esize(d->dtype);
   const size_t np1 = (size_t)(nb + 1) * (nb + 2) / 2;
-  return (size_t)(4 * nb + 3) * g3 * es + (size_t)2 * 4 * m * m * m * 2 * es +
+  return (size_t)sugi_slots(nb, es) * g3 * es + (size_t)2 * 4 * m * m * m * 2 * es +
          shell_c2r_ws_elems(g.grid, m, nb) * 2 * es +
          (contract_partial_doubles(nb + 1, nb) + np1 * nb + (size_t)2 * nb * nb) * 8 + 8192;
 }
@@ -395,9 +399,10 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
   const int64_t n3 = (int64_t)G * G * G, bsz = (int64_t)4 * m * m * m;
   const int np1 = (nb + 1) * (nb + 2) / 2;
   unsigned char* w = align256(reinterpret_cast<unsigned char*>(ws));
-  // [P: nb][ones][W: nb] (the contraction's fields), then [Qa: nb][Qb: nb][g][h]
+  // [P: nb], FP32 [ones][W: nb] (the contraction's fields), then [Qa: nb][Qb: nb][g][h]
   T* fields = reinterpret_cast<T*>(w);
-  cx<T>* spec = reinterpret_cast<cx<T>*>(align256(reinterpret_cast<unsigned char*>(fields + (int64_t)(4 * nb + 3) * n3)));
+  cx<T>* spec = reinterpret_cast<cx<T>*>(
+      align256(reinterpret_cast<unsigned char*>(fields + (int64_t)sugi_slots(nb, sizeof(T)) * n3)));
   cx<T>* ones = reinterpret_cast<cx<T>*>(align256(reinterpret_cast<unsigned char*>(spec + bsz)));
   cx<T>* scr = reinterpret_cast<cx<T>*>(align256(reinterpret_cast<unsigned char*>(ones + bsz)));
   double* partial = reinterpret_cast<double*>(align256(reinterpret_cast<unsigned char*>(scr + shell_c2r_ws_elems(G, m, nb))));
@@ -414,9 +419,9 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
   hipLaunchKernelGGL(k_zero_f64, dim3(1), dim3(256), 0, s, acc, (int64_t)2 * nb * nb);
   CNPC_HIP(hipGetLastError());
   T* slotP = fields;
-  T* slotOne = fields + (int64_t)nb * n3;
+  T* slotOne = fields + (int64_t)nb * n3;  // FP32 alone, as slotW
   T* slotW = slotOne + n3;
-  T* slotQa = slotW + (int64_t)nb * n3;
+  T* slotQa = sizeof(T) == 4 ? slotW + (int64_t)nb * n3 : slotOne;
   T* slotQb = slotQa + (int64_t)nb * n3;
   T* slotG = slotQb + (int64_t)nb * n3;
   T* slotH = slotG + n3;
@@ -424,7 +429,6 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
     hipLaunchKernelGGL((k_fill_real<T>), dim3(1024), dim3(256), 0, s, slotOne, n3, T(1));
     CNPC_HIP(hipGetLastError());
   }
-  const unsigned gw = (unsigned)std::min<int64_t>((n3 + 255) / 256, 8192);
   // leg field (l, m, part) of every shell into a slot, from F_0 (signal) or
   // from ones (harmonic shell indicators of the FFT-method noise)
   const cx<T>* legsrc = F0;
@@ -444,23 +448,20 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
     CNPC_HIP(hipGetLastError());
     return shell_c2r<T>(&dg, m, spec, P->thr.data(), nb + 1, 0, 1, false, slot, scr, s);
   };
-  // sum_x P_i W_j as a GEMM over grid points: the nb + 1 "shell" fields are
-  // P and the all-ones field, the nb columns W (W_j = c1 X_j Z1 + c2 Y_j Z2)
+  // sum_x P_i W_j as a GEMM over grid points (W_j = c1 X_j Z1 + c2 Y_j Z2); FP32: the
+  // nb + 1 "shell" fields are P and the all-ones field, the nb columns W
   double* accum = acc;
   auto contract_add = [&](const T* X, const T* Z1, double c1, const T* Y, const T* Z2, double c2, double coef,
                           int transpose) -> cnpc_status {
     if constexpr (sizeof(T) == 8) {  // W formed inside the contraction (nb <= MAX_COLS shells)
       CNPC_TRY(contract_cross(slotP, X, Z1, c1, Y, Z2, c2, nb, n3, partial, Cm, s));
-      hipLaunchKernelGGL(k_sugi_accum, dim3((nb * nb + 255) / 256), dim3(256), 0, s, Cm, nb, transpose, coef, accum);
+    } else {
+      const unsigned gw = (unsigned)std::min<int64_t>((n3 + 255) / 256, 8192);
+      hipLaunchKernelGGL((k_sugi_w<T>), dim3(gw), dim3(256), 0, s, n3, nb, X, Z1, c1, Y, Z2, c2, slotW);
       CNPC_HIP(hipGetLastError());
-      return CNPC_OK;
-    }
-    hipLaunchKernelGGL((k_sugi_w<T>), dim3(gw), dim3(256), 0, s, n3, nb, X, Z1, c1, Y, Z2, c2, slotW);
-    CNPC_HIP(hipGetLastError());
-    ContractCols cc;
-    cc.ncols = nb;
-    for (int j = 0; j < nb; ++j) cc.field[j] = nb + 1 + j;
-    if constexpr (sizeof(T) == 4) {
+      ContractCols cc;
+      cc.ncols = nb;
+      for (int j = 0; j < nb; ++j) cc.field[j] = nb + 1 + j;
       if (P->prec == CNPC_PREC_BF16X3) {
         CNPC_TRY(contract_mfma(fields, n3, 2 * nb + 1, nb + 1, cc, partial, Cm, s, P->d_pairs, nb));
       } else {
@@ -471,29 +472,25 @@ static cnpc_status sugi_run_t(const cnpc_bispec_plan* P, const cx<T>* F0, const 
     CNPC_HIP(hipGetLastError());
     return CNPC_OK;
   };
-  // sum_x P_i P_j g over the pairs i <= j of the nb fields of P, with g copied
+  // sum_x P_i P_j g over the pairs i <= j of the nb fields of P; FP32: with g copied
   // into the all-ones slot for the call (one column; restored afterwards)
   auto contract_self = [&](double coef) -> cnpc_status {
     if constexpr (sizeof(T) == 8) {
       CNPC_TRY(contract_cross_sym(slotP, slotG, nb, n3, partial, Cm, s));
-      hipLaunchKernelGGL(k_sugi_accum, dim3((nb * nb + 255) / 256), dim3(256), 0, s, Cm, nb, 2, coef, accum);
-      CNPC_HIP(hipGetLastError());
-      return CNPC_OK;
-    }
-    CNPC_HIP(hipMemcpyAsync(slotOne, slotG, sizeof(T) * (size_t)n3, hipMemcpyDeviceToDevice, s));
-    ContractCols cc;
-    cc.ncols = 1;
-    cc.field[0] = nb;
-    if constexpr (sizeof(T) == 4) {
+    } else {
+      CNPC_HIP(hipMemcpyAsync(slotOne, slotG, sizeof(T) * (size_t)n3, hipMemcpyDeviceToDevice, s));
+      ContractCols cc;
+      cc.ncols = 1;
+      cc.field[0] = nb;
       if (P->prec == CNPC_PREC_BF16X3) {
         CNPC_TRY(contract_mfma(fields, n3, nb + 1, nb, cc, partial, Cm, s));
       } else {
         CNPC_TRY(contract_mfma_fp<T>(fields, n3, nb + 1, nb, cc, partial, Cm, s));
       }
+      hipLaunchKernelGGL((k_fill_real<T>), dim3(1024), dim3(256), 0, s, slotOne, n3, T(1));
+      CNPC_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(k_sugi_accum, dim3((nb * nb + 255) / 256), dim3(256), 0, s, Cm, nb, 2, coef, accum);
-    CNPC_HIP(hipGetLastError());
-    hipLaunchKernelGGL((k_fill_real<T>), dim3(1024), dim3(256), 0, s, slotOne, n3, T(1));
     CNPC_HIP(hipGetLastError());
     return CNPC_OK;
   };
