@@ -456,8 +456,8 @@ __device__ void block_exclusive_scan(const U* in, int R, uint32_t* wsum, Emit em
 // cursor = scan, and with bcur the bucket cursors bcur[b] = start[b << bshift].  Slabs of 4096 U tiles,
 // 4 U consecutive ones per thread as 16-byte loads that are all in flight at
 // once (one load at a time took 75 us for the 32768 tiles of a 512^3 mesh, two
-// slabs of U = 4 take 13); ntiles is a power of 8, the arrays are 256-byte
-// aligned.
+// slabs of U = 4 take 13); ntiles is a power of 8 from 512 up (meshes of one bucket
+// have k_small_scan), the arrays are 256-byte aligned.
 template <int U>
 __device__ __forceinline__ void tile_scan(const uint32_t* __restrict__ count, int ntiles, int bshift,
                                           uint32_t* __restrict__ start, uint32_t* __restrict__ cursor,
@@ -501,12 +501,9 @@ __device__ __forceinline__ void tile_scan(const uint32_t* __restrict__ count, in
       q.z = run; run += c[4 * u + 2];
       q.w = run; run += c[4 * u + 3];
       const int tt = t + 4 * u;
-      if (tt + 3 < ntiles) {
+      if (tt < ntiles) {
         *reinterpret_cast<uint4*>(start + tt) = q;
         *reinterpret_cast<uint4*>(cursor + tt) = q;
-      } else if (tt < ntiles) {  // a mesh of one tile
-        start[tt] = q.x;
-        cursor[tt] = q.x;
       }
       if (bcur) {
         const uint32_t r[4] = {q.x, q.y, q.z, q.w};
@@ -563,14 +560,13 @@ __host__ __device__ constexpr size_t partition_lds(int per, int rs, int rcap, in
 }
 
 // One counting-sort step over a chunk of NT * PER particles.
-// SOA: input is the catalog (pos [3][n], optional w), else records.
-// FINE == false: key = bucket (rcap = number of buckets).
-// FINE == true, SOA: key = tile key (rcap = number of tiles, one bucket).
-// FINE == true, records in bucket order: key = tile key; the chunk's keys lie
+// FINE == false: input is the catalog (pos [3][n], optional w), key = bucket (rcap =
+// number of buckets).
+// FINE == true: input is records in bucket order, key = tile key; the chunk's keys lie
 // in [bucket(first) S^3, (bucket(last) + 1) S^3); if that range is wider than
 // rcap the chunk takes one global atomic per particle instead.
 // cursor[key] hands out output slots (initialised to the key's start).
-template <bool SOA, bool FINE, int RS, int PER, int NT>
+template <bool FINE, int RS, int PER, int NT>
 __global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ pos,
                                                             const float* __restrict__ w,
                                                             const Rec<RS>* __restrict__ rin,
@@ -588,7 +584,7 @@ __global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ p
   const int64_t c0 = (int64_t)blockIdx.x * CH;
   const int bshift = 3 * g.ls;
   int klo = 0, R;
-  if (FINE && !SOA) {
+  if (FINE) {
     const Rec<RS> a = rin[c0], b = rin[min(n, c0 + CH) - 1];
     const int kb0 = tile_key(a.v[0], a.v[1], a.v[2], g) >> bshift;
     const int kb1 = tile_key(b.v[0], b.v[1], b.v[2], g) >> bshift;
@@ -604,7 +600,7 @@ __global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ p
     const int64_t i = c0 + (int64_t)k * NT + threadIdx.x;
     key[k] = -1;
     if (i < n) {
-      if (!SOA) {
+      if (FINE) {
         r[k] = rin[i];
       } else {
         r[k].v[0] = pos[i];
@@ -616,7 +612,7 @@ __global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ p
       key[k] = FINE ? t - klo : (t >> bshift);
     }
   }
-  if (FINE && !SOA && R > rcap) {
+  if (FINE && R > rcap) {
     // wide key range: one global slot per particle
 #pragma unroll
     for (int k = 0; k < PER; ++k)
@@ -2029,22 +2025,22 @@ static int partition_per(int rs, int rcap, int nt) {
   return 0;
 }
 
-template <bool SOA, bool FINE, int RS, int NT>
+template <bool FINE, int RS, int NT>
 static void launch_partition_nt(int per, unsigned nblk, size_t lds, const uint32_t* pos, const float* w,
                                 const Rec<RS>* rin, int64_t n, const TileGeom& g, int rcap, uint32_t* cursor,
                                 Rec<RS>* rout, bool pack, hipStream_t s) {
   if (per == 4)
-    hipLaunchKernelGGL((k_partition<SOA, FINE, RS, 4, NT>), dim3(nblk), dim3(NT), lds, s, pos, w, rin, n, g,
+    hipLaunchKernelGGL((k_partition<FINE, RS, 4, NT>), dim3(nblk), dim3(NT), lds, s, pos, w, rin, n, g,
                        rcap, cursor, rout, pack);
   else if (per == 2)
-    hipLaunchKernelGGL((k_partition<SOA, FINE, RS, 2, NT>), dim3(nblk), dim3(NT), lds, s, pos, w, rin, n, g,
+    hipLaunchKernelGGL((k_partition<FINE, RS, 2, NT>), dim3(nblk), dim3(NT), lds, s, pos, w, rin, n, g,
                        rcap, cursor, rout, pack);
   else
-    hipLaunchKernelGGL((k_partition<SOA, FINE, RS, 1, NT>), dim3(nblk), dim3(NT), lds, s, pos, w, rin, n, g,
+    hipLaunchKernelGGL((k_partition<FINE, RS, 1, NT>), dim3(nblk), dim3(NT), lds, s, pos, w, rin, n, g,
                        rcap, cursor, rout, pack);
 }
 
-template <bool SOA, bool FINE, int RS>
+template <bool FINE, int RS>
 static cnpc_status launch_partition(const uint32_t* pos, const float* w, const Rec<RS>* rin, int64_t n,
                                     const TileGeom& g, int rcap, uint32_t* cursor, Rec<RS>* rout, bool pack,
                                     hipStream_t s) {
@@ -2059,9 +2055,9 @@ static cnpc_status launch_partition(const uint32_t* pos, const float* w, const R
   const size_t lds = partition_lds(per, RS, rcap, nt);
   kt_begin(CNPC_KT_SORT, s);
   if (nt == 512)
-    launch_partition_nt<SOA, FINE, RS, 512>(per, nblk, lds, pos, w, rin, n, g, rcap, cursor, rout, pack, s);
+    launch_partition_nt<FINE, RS, 512>(per, nblk, lds, pos, w, rin, n, g, rcap, cursor, rout, pack, s);
   else
-    launch_partition_nt<SOA, FINE, RS, 1024>(per, nblk, lds, pos, w, rin, n, g, rcap, cursor, rout, pack, s);
+    launch_partition_nt<FINE, RS, 1024>(per, nblk, lds, pos, w, rin, n, g, rcap, cursor, rout, pack, s);
   kt_end(CNPC_KT_SORT, s);
   CNPC_HIP(hipGetLastError());
   return CNPC_OK;
@@ -2075,7 +2071,8 @@ static cnpc_status launch_paint_tiles(const cnpc_mesh_desc* d, bool second, int 
   const TileGeom g = tile_geom(d);
   kt_begin(CNPC_KT_PAINT, s);
   if constexpr (sizeof(T) == 4 && RS == 3) {
-    // unit weights: w^2 = w, the second power's blocks are painted alike
+    // unit weights: w^2 = w, the second power's blocks are painted alike (with the other
+    // catalog's weights in cnpc_paint_deinterlace)
     for (int pw = 0; pw < (second ? 2 : 1); ++pw) {
       PaintCats<T, RS> p = pc;
       for (int c = 0; c < ncat; ++c) p.blocks[c] = pc.blocks[c + 2 * pw];
@@ -2164,6 +2161,8 @@ static cnpc_status paint_small(const cnpc_mesh_desc* d, const uint32_t* const* p
   return launch_paint_tiles<T, RS>(d, second, 2, pc, L, s);
 }
 
+// Counting sort with a histogram pass of its own (CNPC_TUNE_SORT_FUSED 1, meshes of
+// several buckets), then the tile painting.
 template <typename T, int RS>
 static cnpc_status sort_and_paint(const cnpc_mesh_desc* d, const uint32_t* pos, const float* w, int64_t n,
                                   int set0, bool second, bool counted, unsigned char* ws,
@@ -2191,12 +2190,8 @@ static cnpc_status sort_and_paint(const cnpc_mesh_desc* d, const uint32_t* pos, 
                      L.ntiles, 3 * g.ls, start, cursor, bcur);
   CNPC_HIP(hipGetLastError());
   const bool pack = packs_records(sizeof(T) == 4, RS, g.shift);  // records of the FP32 painter
-  if (L.nbuckets > 1) {
-    CNPC_TRY((launch_partition<true, false, RS>(pos, w, nullptr, n, g, L.nbuckets, bcur, tmp, false, s)));
-    CNPC_TRY((launch_partition<false, true, RS>(nullptr, nullptr, tmp, n, g, FINE_RCAP, cursor, rec, pack, s)));
-  } else {
-    CNPC_TRY((launch_partition<true, true, RS>(pos, w, nullptr, n, g, L.ntiles, cursor, rec, pack, s)));
-  }
+  CNPC_TRY((launch_partition<false, RS>(pos, w, nullptr, n, g, L.nbuckets, bcur, tmp, false, s)));
+  CNPC_TRY((launch_partition<true, RS>(nullptr, nullptr, tmp, n, g, FINE_RCAP, cursor, rec, pack, s)));
   return paint_sorted<T, RS>(d, second, set0, ws, L, s);
 }
 
@@ -2370,13 +2365,9 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   return paint_sorted<T, RS>(d, second, set0, ws, L, s);
 }
 
-// the one-bucket route of paint_small: both catalogs weighted or both not
-static bool paint_is_small(const PaintLayout& L, const float* gw, const float* rw) {
-  return L.nbuckets == 1 && (gw != nullptr) == (rw != nullptr);
-}
-
-// fused: sums_lmax >= 0 selects paint_small or the fused bucket pass (catalog sums into
-// gs / rs, and with form_norms the norms after both catalogs); counted: tile
+// sums_lmax >= 0: catalog sums into gs / rs and, with form_norms, the norms, along with
+// the sort (paint_small for one bucket, whose catalogs are both weighted or both not;
+// else the fused bucket pass); < 0, several buckets: sort_and_paint, counted: its tile
 // counts already taken.
 template <typename T>
 static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const float* gw,
@@ -2395,7 +2386,7 @@ static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const 
   fa.nt = L.nt;
   fa.nphase = L.nphase;
   fa.nsets = second ? 4 : 2;
-  const bool small = sums_lmax >= 0 && paint_is_small(L, gw, rw);
+  const bool small = L.nbuckets == 1;
   if (small) {
     double* sums_c[2] = {gs, rs};
     double* nm = form_norms ? const_cast<double*>(norms) : nullptr;
@@ -2444,6 +2435,11 @@ static cnpc_status paint_t(const cnpc_mesh_desc* d, const uint32_t* gpos, const 
   return CNPC_OK;
 }
 
+// sums and tile counts along with the sort (meshes of one bucket always)
+static bool fused_sort(const PaintLayout& L) {
+  return L.nbuckets == 1 || tune_value(CNPC_TUNE_SORT_FUSED) != 1;
+}
+
 cnpc_status launch_paint(const cnpc_mesh_desc* d, const uint32_t* gpos, const float* gw,
                          int64_t ngal, const uint32_t* rpos, const float* rw, int64_t nran,
                          const double* norms, void* delta, void* noise, void* ws, size_t ws_bytes,
@@ -2455,10 +2451,10 @@ cnpc_status launch_paint(const cnpc_mesh_desc* d, const uint32_t* gpos, const fl
     return CNPC_EWORKSPACE;
   }
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
-  // several buckets: the bucket pass (one read of the catalog for the tile
-  // counts and the first sort step); one bucket: paint_small (the l = 0 sums of
-  // both are not used here); else the tile count in a read of its own
-  const int lm = (L.nbuckets > 1 ? tune_value(CNPC_TUNE_SORT_FUSED) != 1 : paint_is_small(L, gw, rw)) ? 0 : -1;
+  // one bucket: paint_small; several: the bucket pass (one read of the catalog for the
+  // tile counts and the first sort step) or, by the knob, the tile count in a read of
+  // its own (the l = 0 sums of the first two are not used here)
+  const int lm = fused_sort(L) ? 0 : -1;
   double* sums = reinterpret_cast<double*>(w + L.off_sums);
   if (d->dtype == CNPC_F64)
     return paint_t<double>(d, gpos, gw, ngal, rpos, rw, nran, norms, (double*)delta, (double*)noise, w,
@@ -2506,7 +2502,7 @@ cnpc_status launch_paint_blocks_zr2c(const cnpc_mesh_desc* d, const uint32_t* gp
     return CNPC_EUNSUPPORTED;
   }
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
-  const bool fused = L.nbuckets > 1 && tune_value(CNPC_TUNE_SORT_FUSED) != 1;
+  const bool fused = fused_sort(L);
   if (!fused) {
     // sums and tile counts in a pass of their own, norms before the painting
     uint32_t* count0 = reinterpret_cast<uint32_t*>(w + L.off_count[0]);
@@ -2548,7 +2544,7 @@ cnpc_status launch_paint_fkp(const cnpc_mesh_desc* d, const uint32_t* gpos, cons
   unsigned char* w = reinterpret_cast<unsigned char*>(ws);
   double* gs_ = gsums ? gsums : reinterpret_cast<double*>(w + L.off_sums);
   double* rs_ = rsums ? rsums : reinterpret_cast<double*>(w + L.off_sums) + CNPC_SUMS_LEN;
-  if (L.nbuckets > 1 ? tune_value(CNPC_TUNE_SORT_FUSED) != 1 : paint_is_small(L, gw, rw)) {
+  if (fused_sort(L)) {
     if (d->dtype == CNPC_F64)
       return paint_t<double>(d, gpos, gw, ngal, rpos, rw, nran, norms, (double*)delta, (double*)noise, w, L,
                              false, s, sums_lmax, gs_, rs_);
