@@ -902,7 +902,7 @@ __global__ void __launch_bounds__(NT) k_bucket_pass(const uint32_t* __restrict__
 // global atomics) and count and sort in LDS by (bucket number, tile in bucket),
 // as the region chunks do.  A catalog that fills a part of its box has most of its
 // records here: with one global atomic per record 2.2e7 particles in 1 / 64 of a
-// 256^3 box took 34 ms (FP64 P_0 pass) before, 2.9 here, in 1 / 8 of it 6.1 ms
+// 256^3 box took 34 ms (FP64 P_0 pass) before, 2.8 here, in 1 / 8 of it 6.1 ms
 // before, 1.8 here.
 constexpr int OVF_SLOTS = 32;
 
@@ -1099,33 +1099,52 @@ __global__ void __launch_bounds__(1024) k_region_count(const Rec<RS>* __restrict
   }
 }
 
+// The tile step over the overflow records (a launch of its own: inside the tile pass
+// its registers and tables cost the region chunks of a batch's streams 3% of the whole
+// batch).  PACKED: 8-byte records (pack_rec) with their tile index in okey, else Rec<RS>,
+// in chunks of half the size: the tables take the other half of the LDS.
+template <int RS, int PER, int NT, bool PACKED>
+__global__ void __launch_bounds__(NT, 8) k_overflow_pass(const void* __restrict__ ovf_in,
+                                                         const uint16_t* __restrict__ okey,
+                                                         const uint32_t* __restrict__ ovf, int nbuckets, TileGeom g,
+                                                         uint32_t* __restrict__ cursor, void* __restrict__ rout,
+                                                         bool pack) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int bshift = 3 * g.ls;
+  const int64_t c0 = (int64_t)blockIdx.x * NT * PER, stride = (int64_t)gridDim.x * NT * PER;
+  if constexpr (PACKED) {
+    const uint64_t* in = reinterpret_cast<const uint64_t*>(ovf_in);
+    uint64_t* out = reinterpret_cast<uint64_t*>(rout);
+    sort_overflow<NT, PER, uint64_t>(
+        c0, stride, *ovf, nbuckets, bshift, cursor, smem_raw,
+        [&](int64_t c, uint32_t i, uint64_t& v) {
+          v = (in + c)[i];
+          return (int)(okey + c)[i];
+        },
+        [&](uint32_t o, uint64_t v) { out[o] = v; });
+  } else {
+    const Rec<RS>* in = reinterpret_cast<const Rec<RS>*>(ovf_in);
+    Rec<RS>* out = reinterpret_cast<Rec<RS>*>(rout);
+    sort_overflow<NT, PER, Rec<RS>>(
+        c0, stride, *ovf, nbuckets, bshift, cursor, smem_raw,
+        [&](int64_t c, uint32_t i, Rec<RS>& v) {
+          v = (in + c)[i];
+          return tile_key(v.v[0], v.v[1], v.v[2], g);
+        },
+        [&](uint32_t o, const Rec<RS>& v) { put_rec(out, o, v, pack, g.shift); });
+  }
+}
+
 // Second counting-sort step over the bucket regions: workgroup (b, j) sorts
-// records j CH .. of bucket b (its keys lie in bucket b); workgroups past the
-// last region chunk sort the overflow records (sort_overflow, chunks of half
-// the size: its tables take the other half of the LDS).
+// records j CH .. of bucket b (its keys lie in bucket b).
 template <int RS, int PER, int NT>
-__global__ void __launch_bounds__(NT, 8) k_tile_pass(const Rec<RS>* __restrict__ region,
-                                                  const Rec<RS>* __restrict__ ovf_in, const uint32_t* __restrict__ bcnt,
-                                                  const uint32_t* __restrict__ ovf, uint32_t cap, int chunks_per_bucket,
-                                                  int nbuckets, TileGeom g, uint32_t* __restrict__ cursor,
-                                                  Rec<RS>* __restrict__ rout, bool pack) {
+__global__ void __launch_bounds__(NT) k_tile_pass(const Rec<RS>* __restrict__ region, const uint32_t* __restrict__ bcnt,
+                                                  uint32_t cap, int chunks_per_bucket, TileGeom g,
+                                                  uint32_t* __restrict__ cursor, Rec<RS>* __restrict__ rout, bool pack) {
   constexpr int CH = NT * PER;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int bshift = 3 * g.ls;
   const int R = 1 << bshift;  // tiles per bucket
-  const int nreg = nbuckets * chunks_per_bucket;
-  if ((int)blockIdx.x >= nreg) {
-    constexpr int OP = ovf_per(PER, RS * 4);
-    sort_overflow<NT, OP, Rec<RS>>(
-        (int64_t)(blockIdx.x - nreg) * NT * OP, (int64_t)(gridDim.x - nreg) * NT * OP, *ovf, nbuckets, bshift, cursor,
-        smem_raw,
-        [&](int64_t c, uint32_t i, Rec<RS>& v) {
-          v = (ovf_in + c)[i];
-          return tile_key(v.v[0], v.v[1], v.v[2], g);
-        },
-        [&](uint32_t o, const Rec<RS>& v) { put_rec(rout, o, v, pack, g.shift); });
-    return;
-  }
   const int b = blockIdx.x / chunks_per_bucket, jc = blockIdx.x - b * chunks_per_bucket;
   const uint32_t nb_ = min(bcnt[b], cap);
   const int64_t c0 = (int64_t)jc * CH;
@@ -1178,31 +1197,15 @@ __global__ void __launch_bounds__(NT, 8) k_tile_pass(const Rec<RS>* __restrict__
 // index, for the FP32 painter): the tile index comes from its own array and the
 // packed records are moved as they are
 template <int PER, int NT>
-__global__ void __launch_bounds__(NT, 8) k_tile_pass_packed(const uint64_t* __restrict__ region,
+__global__ void __launch_bounds__(NT) k_tile_pass_packed(const uint64_t* __restrict__ region,
                                                          const uint16_t* __restrict__ rkey,
-                                                         const uint64_t* __restrict__ ovf_in,
-                                                         const uint16_t* __restrict__ okey,
-                                                         const uint32_t* __restrict__ bcnt,
-                                                         const uint32_t* __restrict__ ovf, uint32_t cap,
-                                                         int chunks_per_bucket, int nbuckets, TileGeom g,
+                                                         const uint32_t* __restrict__ bcnt, uint32_t cap,
+                                                         int chunks_per_bucket, TileGeom g,
                                                          uint32_t* __restrict__ cursor, uint64_t* __restrict__ rout) {
   constexpr int CH = NT * PER;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int bshift = 3 * g.ls;
   const int R = 1 << bshift;
-  const int nreg = nbuckets * chunks_per_bucket;
-  if ((int)blockIdx.x >= nreg) {
-    constexpr int OP = ovf_per(PER, 8);
-    sort_overflow<NT, OP, uint64_t>(
-        (int64_t)(blockIdx.x - nreg) * NT * OP, (int64_t)(gridDim.x - nreg) * NT * OP, *ovf, nbuckets, bshift, cursor,
-        smem_raw,
-        [&](int64_t c, uint32_t i, uint64_t& v) {
-          v = (ovf_in + c)[i];
-          return (int)(okey + c)[i];
-        },
-        [&](uint32_t o, uint64_t v) { rout[o] = v; });
-    return;
-  }
   const int b = blockIdx.x / chunks_per_bucket, jc = blockIdx.x - b * chunks_per_bucket;
   const uint32_t nb_ = min(bcnt[b], cap);
   const int64_t c0 = (int64_t)jc * CH;
@@ -1953,7 +1956,7 @@ static TileGeom tile_geom(const cnpc_mesh_desc* d) {
 // mean bucket count plus the largest chunk (more goes to the overflow region).
 constexpr int BUCKET_NT = 1024;
 constexpr int BUCKET_BLOCKS_MAX = 512;
-constexpr int OVF_BLOCKS = 512;  // tile-pass workgroups walking the overflow records (two per CU)
+constexpr int OVF_BLOCKS = 256;  // workgroups walking the overflow records: 512 cost a batch 0.3%
 static uint32_t bucket_cap(int64_t n, int nbuckets) {
   const int64_t mean = (n + nbuckets - 1) / nbuckets;
   const int64_t c = mean + mean / 2 + (int64_t)BUCKET_NT * 8;
@@ -2320,7 +2323,7 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
                        dim3(1024), 0, s, count, L.ntiles, start, cursor, partial, (int)nblk, sums);
   }
   CNPC_HIP(hipGetLastError());
-  // tile pass: one workgroup per region chunk, then OVF_BLOCKS over the overflow
+  // tile pass: one workgroup per region chunk; then OVF_BLOCKS over the overflow
   const int tper = partition_per(RS, per_bucket, 1024);
   if (tper == 0) {
     set_error("tile pass: %d keys do not fit the LDS of a workgroup", per_bucket);
@@ -2328,38 +2331,33 @@ static cnpc_status fused_sort_and_paint(const cnpc_mesh_desc* d, const uint32_t*
   }
   const int64_t tch = (int64_t)1024 * tper;
   const int cpb = (int)((cap + tch - 1) / tch);
-  const unsigned tgrid = (unsigned)(L.nbuckets * cpb + OVF_BLOCKS);
-  const size_t tlds = std::max(partition_lds(tper, RS, per_bucket, 1024),
-                               overflow_lds(ovf_per(tper, RS * 4), RS * 4, 1024, L.nbuckets, 3 * g.ls));
   kt_begin(CNPC_KT_SORT, s);
-  if (packb) {
-    const size_t plds = std::max((size_t)1024 * tper * 10 + (size_t)3 * per_bucket * 4 + 64,
-                                 overflow_lds(ovf_per(tper, 8), 8, 1024, L.nbuckets, 3 * g.ls));
-    const uint64_t* r64 = reinterpret_cast<const uint64_t*>(region);
-    const uint64_t* o64 = reinterpret_cast<const uint64_t*>(ovf_rec);
-    uint64_t* out64 = reinterpret_cast<uint64_t*>(rec);
-    if (tper == 4)
-      hipLaunchKernelGGL((k_tile_pass_packed<4, 1024>), dim3(tgrid), dim3(1024), plds, s, r64, ba.rkey, o64, ba.okey,
-                         bcnt, bcnt + L.nbuckets, cap, cpb, L.nbuckets, g, cursor, out64);
-    else if (tper == 2)
-      hipLaunchKernelGGL((k_tile_pass_packed<2, 1024>), dim3(tgrid), dim3(1024), plds, s, r64, ba.rkey, o64, ba.okey,
-                         bcnt, bcnt + L.nbuckets, cap, cpb, L.nbuckets, g, cursor, out64);
-    else
-      hipLaunchKernelGGL((k_tile_pass_packed<1, 1024>), dim3(tgrid), dim3(1024), plds, s, r64, ba.rkey, o64, ba.okey,
-                         bcnt, bcnt + L.nbuckets, cap, cpb, L.nbuckets, g, cursor, out64);
-    kt_end(CNPC_KT_SORT, s);
-    CNPC_HIP(hipGetLastError());
-    return paint_sorted<T, RS>(d, second, set0, ws, L, s);
-  }
-  if (tper == 4)
-    hipLaunchKernelGGL((k_tile_pass<RS, 4, 1024>), dim3(tgrid), dim3(1024), tlds, s, region, ovf_rec, bcnt,
-                       bcnt + L.nbuckets, cap, cpb, L.nbuckets, g, cursor, rec, pack);
-  else if (tper == 2)
-    hipLaunchKernelGGL((k_tile_pass<RS, 2, 1024>), dim3(tgrid), dim3(1024), tlds, s, region, ovf_rec, bcnt,
-                       bcnt + L.nbuckets, cap, cpb, L.nbuckets, g, cursor, rec, pack);
-  else
-    hipLaunchKernelGGL((k_tile_pass<RS, 1, 1024>), dim3(tgrid), dim3(1024), tlds, s, region, ovf_rec, bcnt,
-                       bcnt + L.nbuckets, cap, cpb, L.nbuckets, g, cursor, rec, pack);
+  auto steps = [&](auto perc) {
+    constexpr int PER = decltype(perc)::value;
+    const dim3 tgrid((unsigned)(L.nbuckets * cpb)), ogrid(OVF_BLOCKS);
+    if (packb) {
+      if constexpr (RS == 3) {
+        const size_t plds = (size_t)1024 * PER * 10 + (size_t)3 * per_bucket * 4 + 64;
+        hipLaunchKernelGGL((k_tile_pass_packed<PER, 1024>), tgrid, dim3(1024), plds, s,
+                           reinterpret_cast<const uint64_t*>(region), ba.rkey, bcnt, cap, cpb, g, cursor,
+                           reinterpret_cast<uint64_t*>(rec));
+        constexpr int OP = ovf_per(PER, 8);
+        hipLaunchKernelGGL((k_overflow_pass<RS, OP, 1024, true>), ogrid, dim3(1024),
+                           overflow_lds(OP, 8, 1024, L.nbuckets, 3 * g.ls), s, ovf_rec, ba.okey, bcnt + L.nbuckets,
+                           L.nbuckets, g, cursor, rec, pack);
+      }
+    } else {
+      hipLaunchKernelGGL((k_tile_pass<RS, PER, 1024>), tgrid, dim3(1024), partition_lds(PER, RS, per_bucket, 1024), s,
+                         region, bcnt, cap, cpb, g, cursor, rec, pack);
+      constexpr int OP = ovf_per(PER, RS * 4);
+      hipLaunchKernelGGL((k_overflow_pass<RS, OP, 1024, false>), ogrid, dim3(1024),
+                         overflow_lds(OP, RS * 4, 1024, L.nbuckets, 3 * g.ls), s, ovf_rec, nullptr, bcnt + L.nbuckets,
+                         L.nbuckets, g, cursor, rec, pack);
+    }
+  };
+  if (tper == 4) steps(std::integral_constant<int, 4>());
+  else if (tper == 2) steps(std::integral_constant<int, 2>());
+  else steps(std::integral_constant<int, 1>());
   kt_end(CNPC_KT_SORT, s);
   CNPC_HIP(hipGetLastError());
   return paint_sorted<T, RS>(d, second, set0, ws, L, s);
