@@ -273,7 +273,10 @@ cnpc_status cnpc_bin_pk_noalloc(const cnpc_mesh_desc* desc, const cnpc_kbins* bi
 /* Shell means of Im F_a(k) F_b(k)^* (odd multipoles: the imaginary-part form
  * of eq. pk_final).  Same arguments, limits and workspace as cnpc_bin_pk with
  * no self terms; for anti-Hermitian products (F_0 F_l^*, l odd) the half-grid
- * weights apply unchanged. */
+ * weights apply unchanged.  With a fixed line of sight n (CNPC_LOS_GLOBAL)
+ * F_l = L_l(k.n) F_0, so the odd rows of an auto spectrum are zero: what comes out
+ * (about 1e-15 of P_0 in FP64, 1e-7 in FP32) is the rounding residue of two
+ * transforms of one mesh, which changes with any change of the rounding. */
 cnpc_status cnpc_bin_pk_im(const cnpc_mesh_desc* desc, const cnpc_kbins* bins, int32_t band,
                            int32_t npairs, const void* const* pa, const void* const* pb,
                            double* means, int64_t* nmodes, double* keff, void* ws, size_t ws_bytes,
@@ -552,17 +555,19 @@ cnpc_status cnpc_ktimer_stop(double* ms_per_class, int64_t* launches_per_class);
  *                          delta and N meshes and transforms them.
  *   CNPC_TUNE_BUCKET       shape of the first sort step of unweighted catalogs
  *                          (0: 1024 threads x 8 particles on one workgroup per
- *                          CU, x 4 or 2 for catalogs too small to fill the CUs;
- *                          1: 1024 x 2 with the next chunk loaded during the
+ *                          CU; 1: 1024 x 2 with the next chunk loaded during the
  *                          current one; 2: 512 x 4, likewise; 3: 1024 x 4 on
- *                          two workgroups per CU).
+ *                          two workgroups per CU; 0 and 3 take 4 or 2 particles
+ *                          for catalogs too small to fill the CUs).
  *   CNPC_TUNE_YLM_BASIS    Y_lm z passes of N = 64 .. 512 with register passes
  *                          (FP32 of 64, 256: bands kz < 4 sqrt(N)): 0
  *                          (default) transforms
  *                          delta R^-L r_z^j, j = 0..L, per parity class of l
  *                          (L its largest l) and forms every field of the
  *                          class from these L + 1 spectra (5 for l = 2, 4);
- *                          1 transforms each field (2l + 1 per l).
+ *                          1 transforms each field (2l + 1 per l).  An observer
+ *                          within a quarter cell of a mesh node: fields formed
+ *                          from directions and transformed one by one.
  *   CNPC_TUNE_SHELL_FUSED  split-BF16 bispectrum contraction on a 128^3 grid
  *                          (at most 24 fields, 128 shell pairs, 32 columns):
  *                          0 (default) runs the shells' c2r z pass inside the

@@ -1338,8 +1338,8 @@ __device__ __forceinline__ void paint_one(unsigned long long* __restrict__ acc, 
 // run on one XCD and read its records from that L2.  Bound by the 64-bit LDS
 // atomics (27 TSC or 8 CIC per particle, phase and power).  256^3 TSC
 // interlaced, 3.0e7 particles: FP64 843 us with conversion calls and one
-// workgroup per CU before, 638 us here; weighted FP32, 1.9e7 particles, both
-// powers: 1270 us before, 932 us here.
+// workgroup per CU before, 669 us here; weighted FP32, 1.9e7 particles, both
+// powers: 1270 us before, 961 us here.
 template <typename T, int ASSIGN, int RS>
 __global__ void __launch_bounds__(1024, 8) k_paint_tiles(PaintCats<T, RS> pc, TileGeom g, int nphase, int npow) {
   const Rec<RS>* __restrict__ rec = pc.rec[blockIdx.y];

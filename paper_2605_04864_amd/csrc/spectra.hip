@@ -34,7 +34,8 @@ static Geo unit_geo(Geo g, int n) {
 
 // Whether those passes may take the mesh: they form r_z along a row by additions,
 // so the direction of a node next to the observer is lost in their rounding (and
-// R^-4 with it); within a quarter of a cell the fields are formed from directions.
+// R^-4 with it); within a quarter of a cell the fields are formed from directions
+// (14 fields of 256^3 FP32: z pass 678 us, 59 by powers).
 static bool ylm_powers_ok(const Geo& g, int n) {
   if (g.global_los) return true;
   double r2 = 0.0;
