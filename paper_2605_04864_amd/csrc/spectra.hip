@@ -1380,9 +1380,22 @@ cnpc_status launch_deinterlace(const cnpc_mesh_desc* d, int band, const void* me
 // W(k) is the product of three values of a table over the band index (one
 // sinpi per axis and mode in FP64 held the kernel to a third of the copy rate),
 // formed once per workgroup: ASM_BLOCKS workgroups at most walk the band.  Band
-// 128, FP32, l = 0, 0, 2: 300 us before, 135 here.
-constexpr int ASM_BLOCKS = 2048;
-template <typename T>
+// 128, FP32, l = 0, 0, 2: 300 us before, 135 here.  STREAM: the 2l + 1 spectra of FP64
+// bands of 128 and more are past every cache; read around them, by three workgroups per
+// CU, they come at 5.9 TB/s (l = 4, band 128: 234 us with a sine per mode and axis, 262
+// through the caches by 2048 workgroups, 228 here; band 256: 2086, 2259, 2038).  Smaller
+// bands and FP32 find part of them in the caches (FP64, l = 4, band 64: 27 us, 31 around).
+constexpr int ASM_BLOCKS = 2048, ASM_STREAM_BLOCKS = 768;
+template <bool STREAM, typename T>
+__device__ __forceinline__ cx<T> ld_spec(const cx<T>* p) {
+  if constexpr (STREAM) {
+    typedef T v2 __attribute__((ext_vector_type(2)));
+    const v2 v = __builtin_nontemporal_load(reinterpret_cast<const v2*>(p));
+    return cx<T>{v.x, v.y};
+  }
+  return *p;
+}
+template <typename T, bool STREAM>
 __global__ void __launch_bounds__(256) k_assemble(int n, int m, int ell, int assign,
                                                   const cx<T>* __restrict__ spec0,
                                                   const cx<T>* __restrict__ ylm, cx<T>* __restrict__ F) {
@@ -1412,10 +1425,10 @@ __global__ void __launch_bounds__(256) k_assemble(int n, int m, int ell, int ass
     const double inv = 1.0 / sqrt((double)n2);
     T re[5], im[5];
     racah_ylm<T>(ell, T(nx * inv), T(ny * inv), T(nz * inv), re, im);
-    cx<T> acc = cscale(ylm[i], re[0]);
+    cx<T> acc = cscale(ld_spec<STREAM>(ylm + i), re[0]);
     for (int mm = 1; mm <= ell; ++mm) {
-      const cx<T> a = ylm[(2 * mm - 1) * bsz + i];
-      const cx<T> b = ylm[(2 * mm) * bsz + i];
+      const cx<T> a = ld_spec<STREAM>(ylm + (2 * mm - 1) * bsz + i);
+      const cx<T> b = ld_spec<STREAM>(ylm + (2 * mm) * bsz + i);
       acc.x += T(2) * (re[mm] * a.x + im[mm] * b.x);
       acc.y += T(2) * (re[mm] * a.y + im[mm] * b.y);
     }
@@ -1426,13 +1439,15 @@ __global__ void __launch_bounds__(256) k_assemble(int n, int m, int ell, int ass
 cnpc_status launch_assemble(const cnpc_mesh_desc* d, int band, int ell, const void* spec0,
                             const void* ylm, void* F, hipStream_t s) {
   const int64_t bsz = (int64_t)4 * band * band * band;
-  const unsigned g = (unsigned)std::min<int64_t>((bsz + 255) / 256, ASM_BLOCKS);
+  const bool stream = d->dtype == CNPC_F64 && band >= 128 && ell > 0;
+  const unsigned g = (unsigned)std::min<int64_t>((bsz + 255) / 256, stream ? ASM_STREAM_BLOCKS : ASM_BLOCKS);
   if (d->dtype == CNPC_F64)
-    hipLaunchKernelGGL((k_assemble<double>), dim3(g), dim3(256), sizeof(double) * 2 * band, s, d->n, band, ell, d->assign,
-                       (const cx<double>*)spec0, (const cx<double>*)ylm, (cx<double>*)F);
+    hipLaunchKernelGGL((stream ? k_assemble<double, true> : k_assemble<double, false>), dim3(g), dim3(256),
+                       sizeof(double) * 2 * band, s, d->n, band, ell, d->assign, (const cx<double>*)spec0,
+                       (const cx<double>*)ylm, (cx<double>*)F);
   else
-    hipLaunchKernelGGL((k_assemble<float>), dim3(g), dim3(256), sizeof(double) * 2 * band, s, d->n, band, ell, d->assign,
-                       (const cx<float>*)spec0, (const cx<float>*)ylm, (cx<float>*)F);
+    hipLaunchKernelGGL((k_assemble<float, false>), dim3(g), dim3(256), sizeof(double) * 2 * band, s, d->n, band, ell,
+                       d->assign, (const cx<float>*)spec0, (const cx<float>*)ylm, (cx<float>*)F);
   CNPC_HIP(hipGetLastError());
   return CNPC_OK;
 }
