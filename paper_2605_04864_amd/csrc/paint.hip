@@ -180,11 +180,11 @@ __device__ __forceinline__ void sums_add(double* acc, uint32_t px, uint32_t py, 
   }
 }
 
-// particles of one of nblk workgroups of a sums pass: consecutive ones
-__host__ __device__ __forceinline__ int64_t sums_range(int64_t n, int nblk) { return (n + nblk - 1) / nblk; }
-
 // Catalog sums of one workgroup, block `blk` of `nblk` (LMAX: Y_lm sums for
-// l <= LMAX, 0, 2 or 4; the others stay zero) into partial[blk], and the tile
+// l <= LMAX, 0, 2 or 4; the others stay zero; its particles are those of every
+// nblk-th run of SUMS_THREADS, so that the workgroups read one stretch of the catalog
+// at a time: with a range of its own for each, 3e8 particles took 1274 us, 1183
+// here) into partial[blk], and the tile
 // histogram of its particles: with `hist` stored there (at most 64 tiles), else
 // added to ca.count.
 constexpr int SMALL_TILES = 64;  // tiles of a mesh of one bucket, at most
@@ -206,8 +206,8 @@ __device__ __forceinline__ void catalog_sums_block(const uint32_t* __restrict__ 
   // U particles per thread and trip: all their loads are issued before any of
   // them is used (fewer for the larger register sets of l > 0)
   constexpr int U = LMAX == 0 ? 4 : (LMAX == 2 ? 2 : 1);
-  const int64_t stride = blockDim.x, c0 = sums_range(n, nblk) * blk, c1 = min(n, c0 + sums_range(n, nblk));
-  for (int64_t i0 = c0 + threadIdx.x; i0 < c1; i0 += U * stride) {
+  const int64_t stride = (int64_t)nblk * SUMS_THREADS;
+  for (int64_t i0 = (int64_t)blk * SUMS_THREADS + threadIdx.x; i0 < n; i0 += U * stride) {
     uint32_t px[U], py[U], pz[U];
     float wv[U];
 #pragma unroll
@@ -215,7 +215,7 @@ __device__ __forceinline__ void catalog_sums_block(const uint32_t* __restrict__ 
       const int64_t i = i0 + u * stride;
       px[u] = py[u] = pz[u] = 0u;
       wv[u] = 1.0f;
-      if (i < c1) {
+      if (i < n) {
         px[u] = ld_stream(pos + i);
         py[u] = ld_stream(pos + n + i);
         pz[u] = ld_stream(pos + 2 * n + i);
@@ -224,7 +224,7 @@ __device__ __forceinline__ void catalog_sums_block(const uint32_t* __restrict__ 
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (i0 + u * stride >= c1) break;
+      if (i0 + u * stride >= n) break;
       if (count) {
         const int t = tile_key(px[u], py[u], pz[u], ca.g);
         if (lds) atomicAdd(&lcount[t], 1u);
@@ -648,8 +648,8 @@ __global__ void __launch_bounds__(NT) k_partition(const uint32_t* __restrict__ p
 }
 
 // The one sort step of a mesh of one tile bucket, both catalogs in one launch:
-// workgroup b sorts the particles of sums workgroup b, whose place in every tile
-// k_small_scan has left in hist[b], chunk by chunk (a cursor per tile in LDS; one
+// workgroup b sorts the particles of sums workgroup b (every nblk-th run of 1024),
+// whose place in every tile k_small_scan has left in hist[b], PER runs at a time (a cursor per tile in LDS; one
 // atomic per chunk and tile on 64 shared counters took 25 us for 2.2e6 particles,
 // 15 us here).
 template <int RS, int PER>
@@ -662,19 +662,20 @@ __global__ void __launch_bounds__(1024) k_partition2(SmallPair sp, TileGeom g, i
   uint16_t* skey = reinterpret_cast<uint16_t*>(smem_raw + (size_t)CH * RS * 4);  // [CH]
   __shared__ uint32_t hist[SMALL_TILES], lstart[SMALL_TILES], gbase[SMALL_TILES];
   Rec<RS>* rout = reinterpret_cast<Rec<RS>*>(c.rec);
-  const int64_t r0 = sums_range(c.n, c.nblk) * blockIdx.x, r1 = min(c.n, r0 + sums_range(c.n, c.nblk));
+  static_assert(NT == SUMS_THREADS, "runs of the sums pass");
+  const int64_t stride = (int64_t)c.nblk * NT;
   if (threadIdx.x < SMALL_TILES) {
     gbase[threadIdx.x] = (int)threadIdx.x < ntiles ? c.hist[(int64_t)blockIdx.x * SMALL_TILES + threadIdx.x] : 0u;
     hist[threadIdx.x] = 0u;
   }
   __syncthreads();
-  for (int64_t c0 = r0; c0 < r1; c0 += CH) {
+  for (int64_t c0 = (int64_t)blockIdx.x * NT; c0 < c.n; c0 += PER * stride) {
     Rec<RS> r[PER];
     int key[PER];
     uint32_t rank[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {  // clamped straight-line loads, all in flight at once
-      const int64_t i = min(c0 + (int64_t)k * NT + threadIdx.x, r1 - 1);
+      const int64_t i = min(c0 + k * stride + threadIdx.x, c.n - 1);
       r[k].v[0] = c.pos[i];
       r[k].v[1] = c.pos[c.n + i];
       r[k].v[2] = c.pos[2 * c.n + i];
@@ -682,7 +683,7 @@ __global__ void __launch_bounds__(1024) k_partition2(SmallPair sp, TileGeom g, i
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      key[k] = c0 + (int64_t)k * NT + threadIdx.x < r1 ? tile_key(r[k].v[0], r[k].v[1], r[k].v[2], g) : -1;
+      key[k] = c0 + k * stride + threadIdx.x < c.n ? tile_key(r[k].v[0], r[k].v[1], r[k].v[2], g) : -1;
       if (key[k] >= 0) rank[k] = atomicAdd(&hist[key[k]], 1u);
     }
     __syncthreads();
@@ -704,7 +705,7 @@ __global__ void __launch_bounds__(1024) k_partition2(SmallPair sp, TileGeom g, i
         skey[slot] = (uint16_t)key[k];
       }
     __syncthreads();
-    const int cnt = (int)min((int64_t)CH, r1 - c0);
+    const int cnt = (int)(lstart[SMALL_TILES - 1] + hist[SMALL_TILES - 1]);
     for (int j = threadIdx.x; j < cnt; j += NT) {
       const int kk = skey[j];
       rout[gbase[kk] + (j - lstart[kk])] = stage[j];
@@ -2154,8 +2155,8 @@ static cnpc_status paint_small(const cnpc_mesh_desc* d, const uint32_t* const* p
   CNPC_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_small_scan, dim3(3), dim3(1024), 0, s, sp, L.ntiles, n[0], d->boxsize, norms);
   CNPC_HIP(hipGetLastError());
-  // chunks of 4 particles per thread for ranges of more than one chunk of 1
-  const int per = sums_range(nmax, sums_blocks(nmax)) > 1024 ? 4 : 1;
+  // 4 runs at a time where a workgroup has more than one
+  const int per = nmax > (int64_t)sums_blocks(nmax) * SUMS_THREADS ? 4 : 1;
   kt_begin(CNPC_KT_SORT, s);
   hipLaunchKernelGGL((per == 4 ? k_partition2<RS, 4> : k_partition2<RS, 1>), dim3((unsigned)nblk, 2), dim3(1024),
                      (size_t)1024 * per * (RS * 4 + 2), s, sp, g, L.ntiles);
